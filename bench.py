@@ -33,7 +33,7 @@ PEAK_FP32 = 157.3e12   # MI355X vector FP32, FLOP/s
 # for a 1 GiB device copy (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0;
 # profiles/path_kernel_gpu_n20_counters.md), keyed by the hash of the kernel
 # sources they were taken on; any other hash reports null.
-TRAFFIC_BYTES = {"92e05cbf6a5b5222": {"full": 146993080, "picard": 166064311}}
+TRAFFIC_BYTES = {"e9f627cb22b6e166": {"full": 34074336, "picard": 33973328}}
 KERNEL_SOURCES = ["paper_1006_3340_amd/csrc/path_kernel.hpp",
                   "paper_1006_3340_amd/csrc/lll_device.hpp"]
 MLP_SOURCES = ["paper_1006_3340_amd/csrc/mlp_path.hip", "paper_1006_3340_amd/csrc/mlp.hpp",
@@ -43,11 +43,11 @@ MLP_SOURCES = ["paper_1006_3340_amd/csrc/mlp_path.hip", "paper_1006_3340_amd/csr
 # rocprofv3 --pmc figures of the surrogate pricing kernel at 2^20 paths
 # (profiles/mlp_kernels_mlp_n40_mfma_counters.md), by source hash: a changed
 # kernel reports none
-MLP_COUNTERS = {"653b1a0fa29f8bbc": {
+MLP_COUNTERS = {"970b3c9d1c09baf0": {
     "source": "profiles/mlp_kernels_mlp_n40_mfma_counters.md",
-    "mlp_path_kernel_ms": 524.01, "clock_ghz": 2.37,
-    "counted_mfma_flop": 2.178e+14, "counted_mfma_tflops": 415.6,
-    "mfma_busy": 0.167, "valu_busy": 0.853, "trans_share_of_valu": 0.222}}
+    "mlp_path_kernel_ms": 523.11, "clock_ghz": 2.38,
+    "counted_mfma_flop": 2.178e+14, "counted_mfma_tflops": 416.3,
+    "mfma_busy": 0.167, "valu_busy": 0.855, "trans_share_of_valu": 0.221}}
 
 
 def source_hash(sources) -> str:
@@ -77,8 +77,8 @@ Q = 64
 METRIC = "path-steps/s: full Euler vs Picard vs MLP drift, at <=1e-4 rel caplet error"
 
 
-def flops_per_path_step(scheme: str, n: int) -> int:
-    """Algorithmic FP32 flops of one Euler step with n live rates (FMA = 2).
+def flops_per_path_step(scheme: str, n: int, q: int = Q) -> int:
+    """FP32 flops of one Euler step with n live rates and q nodes (FMA = 2).
     FULL / PICARD, per quadrature node: the top rate's R = ell E (1), the n - 1
     coupled rates' C += W E R (2 each) and the n - 2 rates between them and
     the lowest live rate advancing R = R + ell E (1 + R) (4 each), i.e.
@@ -86,7 +86,7 @@ def flops_per_path_step(scheme: str, n: int) -> int:
     which also advances its predictor) and 40 for the increment.
     SECOND_ORDER: 6n - 8 per node (the truncated product carries two sums).
     FIRST_ORDER: n (n - 1) / 2 FMAs of the closed-form sums.  FROZEN: the update."""
-    node = Q * (6 * n - 9) if n >= 2 else 0
+    node = q * (6 * n - 9) if n >= 2 else 0
     if scheme == "full":
         return node + 8 * n + 40
     if scheme == "picard":
@@ -96,13 +96,22 @@ def flops_per_path_step(scheme: str, n: int) -> int:
     if scheme == "first_order":
         return n * (n - 1) + 8 * n + 40
     if scheme == "second_order":
-        return (Q * (6 * n - 8) if n >= 2 else 0) + 8 * n + 40
+        return (q * (6 * n - 8) if n >= 2 else 0) + 8 * n + 40
     raise ValueError(scheme)
 
 
-def flops_per_path(ts, scheme: str) -> int:
+def flops_per_path(ts, scheme: str, nodes=None) -> int:
+    """Flops of one path; nodes: the node count of every period (64 if None)."""
     s, N = ts.steps_per_period, ts.n_rates
-    return sum(s * flops_per_path_step(scheme, N - m) for m in range(N))
+    q = [Q] * N if nodes is None else nodes
+    return sum(s * flops_per_path_step(scheme, N - m, int(q[m])) for m in range(N))
+
+
+def rule_nodes(lll, ts):
+    """Node count of every period's Gauss rule, as an FP32 plan of ts uses it:
+    the rates below count the operations the kernels execute."""
+    with lll.Plan(ts, precision=lll.FP32, max_paths=1) as plan:
+        return plan.nodes()["count"]
 
 
 GOLDEN = os.path.join(ROOT, "tests", "golden")
@@ -167,29 +176,29 @@ def cpu_baseline(ts, n_sample: int, schemes) -> dict:
                            "sample": f"{n1} paths, {dt1:.1f} s"}}
 
 
-def adjoint_flops_per_path(ts) -> int:
+def adjoint_flops_per_path(ts, nodes) -> int:
     """Algorithmic FP32 flops of the Greeks pass per path: the FULL forward pass,
     then for every caplet c (n = N - c rates carried) and every step up to its
     fixing, one recomputed FULL step plus the reverse step (18 flops per
     (rate, node): suffix product 3, F recursion 5, the adjoints of ell and E 10)."""
     N, s = ts.n_rates, ts.steps_per_period
-    total = flops_per_path(ts, "full")
+    total = flops_per_path(ts, "full", nodes)
     for c in range(N):
         n = N - c
-        per_step = flops_per_path_step("full", n) + 18 * Q * n + 10 * n
-        total += (c + 1) * s * per_step
+        for q in nodes[:c + 1]:
+            total += s * (flops_per_path_step("full", n, int(q)) + 18 * int(q) * n + 10 * n)
     return total
 
 
-def vjp_flops_per_path(ts) -> int:
+def vjp_flops_per_path(ts, nodes) -> int:
     """Algorithmic FP32 flops of the vector-Jacobian product per path: the FULL
     forward pass, then for every period m (n = N - m rates carried) and each of
     its steps one recomputed FULL step plus the reverse step."""
     N, s = ts.n_rates, ts.steps_per_period
-    total = flops_per_path(ts, "full")
+    total = flops_per_path(ts, "full", nodes)
     for m in range(N):
-        n = N - m
-        total += s * (flops_per_path_step("full", n) + 18 * Q * n + 10 * n)
+        n, q = N - m, int(nodes[m])
+        total += s * (flops_per_path_step("full", n, q) + 18 * q * n + 10 * n)
     return total
 
 
@@ -211,9 +220,10 @@ def bench_adjoint(lll, stream, n: int = 1 << 20) -> dict:
         r = plan.greeks_vjp_results(stream)
     if not np.all(np.isfinite(g["dP_dL0"])):
         raise RuntimeError("non-finite Greeks")
-    fl = adjoint_flops_per_path(ts) * n
+    nodes = rule_nodes(lll, ts)
+    fl = adjoint_flops_per_path(ts, nodes) * n
     t = ms / 1e3
-    fv = vjp_flops_per_path(ts) * n
+    fv = vjp_flops_per_path(ts, nodes) * n
     tv = ms_vjp / 1e3
     ref = w @ g["dP_dL0"]
     return {"workload": ts.name, "n_paths": n, "ms": ms,
@@ -302,8 +312,9 @@ def bench_mlp(lll, stream, n: int = 1 << 20, train_steps: int = 3000) -> dict:
     out["mlp"].update({"mfma_tflops": mf * n / t / 1e12, "frac_bf16_peak": mf * n / t / PEAK_BF16,
                        "valu_tflops": va * n / t / 1e12, "frac_fp32_peak": va * n / t / PEAK_FP32,
                        "counters": MLP_COUNTERS.get(source_hash(MLP_SOURCES))})
+    nodes = rule_nodes(lll, ts)
     for name in ("full", "picard", "first_order", "second_order"):
-        fl = flops_per_path(ts, name) * n
+        fl = flops_per_path(ts, name, nodes) * n
         out[name]["frac_fp32_peak"] = fl / (out[name]["kernel_ms"] / 1e3) / PEAK_FP32
     return out
 
@@ -332,6 +343,7 @@ def bench_reference_schemes(lll, plan, ts, n, stream) -> dict:
     plan.execute(lll.FULL, n, seed=1, stream=stream)
     full = plan.results(stream)["price"]
     live = full > 0.0
+    nodes = rule_nodes(lll, ts)
     out = {}
     for name in ("frozen", "first_order", "second_order"):
         plan.execute(lll.SCHEMES[name], n, seed=1, stream=stream)   # warmup
@@ -342,7 +354,7 @@ def bench_reference_schemes(lll, plan, ts, n, stream) -> dict:
         t = float(np.median(ms)) / 1e3
         price = plan.results(stream)["price"]
         out[name] = {"path_kernel_ms": t * 1e3, "path_steps_per_s": n * ts.n_steps / t,
-                     "frac_fp32_peak": flops_per_path(ts, name) * n / t / PEAK_FP32,
+                     "frac_fp32_peak": flops_per_path(ts, name, nodes) * n / t / PEAK_FP32,
                      "max_rel_err_vs_full": float(np.max(np.abs(price[live] / full[live] - 1)))}
     return out
 
@@ -480,6 +492,7 @@ def bench_maturity_parallel(lll, stream) -> dict:
     out = {}
     for wl, n in (("mp_n60", 10000), ("mlp_n40", 10000), ("gpu_n20", 10000), ("mlp_n40", 1 << 17)):
         ts = workloads.WORKLOADS[wl]()
+        nodes = rule_nodes(lll, ts)
         names = ["picard_mp"] + ([] if ts.n_rates > lll.N_MAX else ["full", "picard"])
         res, prices = {}, {}
         with lll.Plan(ts, precision=lll.FP32, max_paths=n) as plan:
@@ -492,7 +505,8 @@ def bench_maturity_parallel(lll, stream) -> dict:
                     ms.append(plan.timing()["paths"])
                 t = float(np.median(ms)) / 1e3
                 prices[name] = plan.results(stream)["price"]
-                fl = flops_per_path(ts, "picard" if name == "picard_mp" else name) * n
+                fl = (flops_per_path(ts, "picard") if name == "picard_mp"  # on the 64 nodes
+                      else flops_per_path(ts, name, nodes)) * n
                 res[name] = {"ms": t * 1e3, "path_steps_per_s": n * ts.n_steps / t,
                              "fp32_tflops": fl / t / 1e12, "frac_fp32_peak": fl / t / PEAK_FP32}
         for ref in ("picard", "full"):
@@ -509,6 +523,7 @@ def bench_batched(lll, stream, schemes, n_each: int = 1 << 18, reps: int = 2) ->
     """64 independent structures in one persistent launch: kernel time (HIP events
     recorded by the library), path-steps/s and FP32 fraction of peak."""
     structs = workloads.batched()
+    nodes = [rule_nodes(lll, ts) for ts in structs]
     out = {"workload": "batched_64", "n_structures": len(structs), "paths_each": n_each}
     with lll.Batch(structs, max_paths_each=n_each) as b:
         b.set_timing(True)
@@ -520,7 +535,7 @@ def bench_batched(lll, stream, schemes, n_each: int = 1 << 18, reps: int = 2) ->
                 ms.append(b.timing())
             t = float(np.mean(ms)) / 1e3
             steps = sum(ts.n_steps for ts in structs) * n_each
-            fl = sum(flops_per_path(ts, name) for ts in structs) * n_each
+            fl = sum(flops_per_path(ts, name, q) for ts, q in zip(structs, nodes)) * n_each
             out[name] = {"kernel_ms": t * 1e3, "path_steps_per_s": steps / t,
                          "fp32_tflops": fl / t / 1e12, "frac_fp32_peak": fl / t / PEAK_FP32}
     return out
@@ -618,10 +633,11 @@ def main(argv=None) -> int:
 
     path_steps = n * ts.n_steps * len(schemes) * args.steps
     value = path_steps / elapsed
+    nodes = rule_nodes(lll, ts)
     per_scheme = {}
     for name in schemes:
         ms = float(np.mean([r["paths"] for r in rec[name]]))
-        fl = flops_per_path(ts, name) * n
+        fl = flops_per_path(ts, name, nodes) * n
         per_scheme[name] = {
             "path_kernel_ms": ms,
             "precompute_ms": float(np.mean([r["precompute"] for r in rec[name]])),
@@ -631,7 +647,7 @@ def main(argv=None) -> int:
             "frac_fp32_peak": fl / (ms / 1e3) / PEAK_FP32,
         }
     dom = schemes[0]
-    fl_dom = flops_per_path(ts, dom) * n
+    fl_dom = flops_per_path(ts, dom, nodes) * n
     ms_dom = per_scheme[dom]["path_kernel_ms"]
     out = {
         "metric": METRIC,
@@ -664,6 +680,7 @@ def main(argv=None) -> int:
                      "fma_probe_tflops": fma_probe,
                      "mix_ceiling_tflops": mix_probe,
                      "frac_of_mix_ceiling": fl_dom / (ms_dom / 1e3) / 1e12 / mix_probe,
+                     "rule_nodes": [int(q) for q in nodes],
                      "kernel_hash": kernel_hash()},
         "schemes": per_scheme,
         "wall_s": wall,

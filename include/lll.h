@@ -547,6 +547,16 @@ int lll_plan_increments(lll_plan *plan, int k, int64_t p0, int64_t n, uint64_t s
 int lll_plan_tables(lll_plan *plan, double *x_host, double *w_host, double *kappa_host,
                     double *E_host, double *b0_host, void *stream);
 
+/* The nodes on which the kernels integrate the coupling.  The 64-node rule of
+ * lll_plan_tables is a discrete measure; each accrual period m uses the Gauss
+ * rule of it with the fewest nodes that reproduces its coupling integrals to
+ * 2^-30 (FP32 plans) or 2^-47 (FP64 plans) of their value at every state, and
+ * the 64 nodes themselves where no such rule of at most 24 nodes exists:
+ * count_host[N] nodes per period, x_host[N][Q] and w_host[N][Q] (entries past
+ * the count undefined).  Runs the plan's precompute; any pointer may be NULL. */
+int lll_plan_nodes(lll_plan *plan, int32_t *count_host, double *x_host, double *w_host,
+                   void *stream);
+
 /* Drift b(t_k, T_i) of the live rates at step k for n given rate vectors
  * L_host[n][N], computed by the path kernel's own drift code in the plan's
  * precision; b_host[n][N] (entries of fixed rates are 0).  LLL_EUNSUPPORTED

@@ -27,7 +27,7 @@ N_MAX, N_MAX_MP, N_MAX_FP64, N_MAX_EXACT, S_MAX, Q = 40, 64, 24, 20, 8, 64
 EXPORTS = ["lll_version", "lll_last_error", "lll_plan_create", "lll_plan_execute",
            "lll_plan_results", "lll_plan_sums", "lll_plan_partials", "lll_plan_destroy",
            "lll_price_caplets", "lll_philox", "lll_sampler_math", "lll_plan_increments",
-           "lll_plan_tables",
+           "lll_plan_tables", "lll_plan_nodes",
            "lll_plan_drift", "lll_plan_set_timing", "lll_plan_timing", "lll_batch_create",
            "lll_batch_execute", "lll_batch_results", "lll_batch_set_timing", "lll_batch_timing",
            "lll_batch_destroy", "lll_plan_greeks", "lll_plan_greeks_results", "lll_plan_greeks_vjp",
@@ -104,6 +104,7 @@ def load():
     lib.lll_sampler_math.argtypes = [ctypes.c_int, dp, i64, dp, vp]
     lib.lll_plan_increments.argtypes = [vp, i32, i64, i64, u64, dp, dp, vp]
     lib.lll_plan_tables.argtypes = [vp, dp, dp, dp, dp, dp, vp]
+    lib.lll_plan_nodes.argtypes = [vp, ctypes.POINTER(ctypes.c_int32), dp, dp, vp]
     lib.lll_plan_drift.argtypes = [vp, i32, dp, i64, dp, vp]
     fp = ctypes.POINTER(ctypes.c_float)
     i64p = ctypes.POINTER(ctypes.c_int64)
@@ -370,6 +371,14 @@ class Plan:
         _check(self.lib.lll_plan_tables(self.h, _dp(x), _dp(w), _dp(kap), _dp(E), _dp(b0),
                                         stream_handle(stream)))
         return {"x": x, "w": w, "kappa": kap, "E": E, "b0": b0}
+
+    def nodes(self, stream=None) -> dict:
+        """lll_plan_nodes: node count per period and the periods' Gauss rules."""
+        count = np.zeros(self.N, dtype=np.int32)
+        x = np.zeros((self.N, Q)); w = np.zeros((self.N, Q))
+        _check(self.lib.lll_plan_nodes(self.h, count.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
+                                       _dp(x), _dp(w), stream_handle(stream)))
+        return {"count": count, "x": x, "w": w}
 
     def drift(self, k: int, L: np.ndarray, stream=None) -> np.ndarray:
         L = np.ascontiguousarray(np.atleast_2d(np.asarray(L, dtype=np.float64)))

@@ -149,6 +149,7 @@ hipError_t dalloc(T **p, size_t n) {
 
 void free_tables(lll::DeviceTables &d) {
     void *ptrs[] = {d.tenor, d.delta, d.L0, d.vol, d.strikes, d.x, d.w, d.kappa, d.E, d.b0,
+                    d.gx,
                     d.steps, d.lam_pm, d.vol_base, d.ew, d.lam, d.drift0, d.frozen, d.dt, d.cinv, d.k2, d.kex, d.xex, d.L0s,
                     d.deltas, d.partials, d.chunks, d.sums, d.results};
     for (void *p : ptrs)
@@ -220,7 +221,8 @@ int create_plan(const lll_term_structure *ts, int precision, int64_t max_paths, 
         if (e == hipSuccess) e = dalloc(ptr, n);
     };
     A(&d.tenor, N); A(&d.delta, N); A(&d.L0, N); A(&d.vol, K * N); A(&d.strikes, N * S);
-    A(&d.x, lll::kQSize); A(&d.w, lll::kQSize); A(&d.kappa, K * N); A(&d.E, K * N * lll::kQSize);
+    A(&d.x, lll::kQSize); A(&d.w, lll::kQSize); A(&d.kappa, K * N);
+    A(&d.gx, 2 * N * lll::kQSize + (K + 1) / 2);  // with gw and nq behind it
     A(&d.b0, K * N); A(&d.steps, 4 * N); A(&d.lam_pm, 4);
     auto AB = [&](void **ptr, size_t n) {
         if (e == hipSuccess) e = hipMalloc(ptr, n * esz + 16);
@@ -232,6 +234,8 @@ int create_plan(const lll_term_structure *ts, int precision, int64_t max_paths, 
     A(&d.chunks, (size_t)p->max_chunks * N * nstat);
     A(&d.sums, N * nstat);
     A(&d.results, 3 * N * S + 2 * N);
+    d.gw = d.gx + N * lll::kQSize;
+    d.nq = reinterpret_cast<int *>(d.gw + N * lll::kQSize);
     if (e != hipSuccess) {
         free_tables(d);
         delete p;
@@ -591,9 +595,15 @@ int lll_plan_tables(lll_plan *plan, double *x_host, double *w_host, double *kapp
                     double *E_host, double *b0_host, void *stream) {
     if (!plan) return fail(LLL_EINVAL, "plan is NULL");
     hipStream_t st = as_stream(stream);
-    hipError_t e = lll::launch_precompute(*plan, st);
-    if (e != hipSuccess) return hip_fail(e, "precompute launch");
     const size_t K = plan->K, N = plan->N, Q = lll::kQSize;
+    // the 64-node tables are made only for a plan that holds E: for this call
+    const bool held = plan->d.E != nullptr;
+    hipError_t e = held ? hipSuccess : dalloc(&plan->d.E, K * N * Q);
+    if (e != hipSuccess) {
+        plan->d.E = nullptr;
+        return fail(LLL_ENOMEM, "table E: %s", hipGetErrorString(e));
+    }
+    e = lll::launch_precompute(*plan, st);
     auto D2H = [&](double *dst, const double *src, size_t n) {
         if (dst && e == hipSuccess)
             e = hipMemcpyAsync(dst, src, n * sizeof(double), hipMemcpyDeviceToHost, st);
@@ -603,8 +613,32 @@ int lll_plan_tables(lll_plan *plan, double *x_host, double *w_host, double *kapp
     D2H(kappa_host, plan->d.kappa, K * N);
     D2H(E_host, plan->d.E, K * N * Q);
     D2H(b0_host, plan->d.b0, K * N);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const hipError_t done = hipStreamSynchronize(st);
+    if (!held) {
+        (void)hipFree(plan->d.E);
+        plan->d.E = nullptr;
+    }
+    if (e == hipSuccess) e = done;
     if (e != hipSuccess) return hip_fail(e, "reading tables");
+    return LLL_OK;
+}
+
+int lll_plan_nodes(lll_plan *plan, int32_t *count_host, double *x_host, double *w_host,
+                   void *stream) {
+    if (!plan) return fail(LLL_EINVAL, "plan is NULL");
+    hipStream_t st = as_stream(stream);
+    const size_t N = plan->N, K = plan->K, Q = lll::kQSize;
+    std::vector<int> nq(K);
+    hipError_t e = lll::launch_precompute(*plan, st);
+    auto D2H = [&](void *dst, const void *src, size_t bytes) {
+        if (dst && e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
+    };
+    D2H(nq.data(), plan->d.nq, K * sizeof(int));
+    D2H(x_host, plan->d.gx, N * Q * sizeof(double));
+    D2H(w_host, plan->d.gw, N * Q * sizeof(double));
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return hip_fail(e, "reading nodes");
+    for (size_t m = 0; count_host && m < N; ++m) count_host[m] = nq[m * plan->s];
     return LLL_OK;
 }
 

@@ -32,16 +32,16 @@ namespace {
 // NIG: kappa'(u) = mu_H + delta (beta + u) / sqrt(alpha^2 - (beta + u)^2).
 __global__ void __launch_bounds__(64) setup_adjoint_tables_kernel(
     const double *__restrict__ tenor, const double *__restrict__ L0, const double *__restrict__ vol,
-    const double *__restrict__ x_in, const double *__restrict__ w_in, int N, int s, int off,
-    int nmax, double alpha, double beta, double delta_nig, float *__restrict__ xe,
+    const double *__restrict__ gx, const double *__restrict__ gw, const int *__restrict__ nq, int N,
+    int s, int off, int nmax, double alpha, double beta, double delta_nig, float *__restrict__ xe,
     float *__restrict__ dkap, float *__restrict__ w32, double *__restrict__ inv_L0) {
     const int k = blockIdx.x;
     const int q = threadIdx.x;
     const int m = k / s;
     const double Ta = (m == 0) ? 0.0 : tenor[m - 1];
     const double dt = (tenor[m] - Ta) / s;
-    const double xq = x_in[q];
-    for (int j = 0; j < nmax; ++j) {
+    const double xq = gx[m * kQ + q];
+    for (int j = 0; j < nmax && q < nq[k]; ++j) {
         const int r = j - off;
         double v = 0.0;
         if (r >= m) v = xq * exp(vol[(size_t)k * N + r] * xq);
@@ -58,8 +58,8 @@ __global__ void __launch_bounds__(64) setup_adjoint_tables_kernel(
         }
         dkap[(size_t)k * nmax + q] = static_cast<float>(d);
     }
+    if (k == m * s && q < nq[k]) w32[m * kQ + q] = static_cast<float>(gw[m * kQ + q]);
     if (k == 0) {
-        w32[q] = static_cast<float>(w_in[q]);
         if (q < nmax) inv_L0[q] = (q - off >= 0) ? 1.0 / L0[q - off] : 0.0;
     }
 }
@@ -160,7 +160,7 @@ hipError_t greeks_alloc(lll_plan &p) {
     };
     A((void **)&g.xe, K * kQSize * NM * sizeof(float));
     A((void **)&g.dkap, K * NM * sizeof(float));
-    A((void **)&g.w32, kQSize * sizeof(float));
+    A((void **)&g.w32, N * kQSize * sizeof(float));
     A((void **)&g.inv_L0, NM * sizeof(double));
     A((void **)&g.ckpt, N * (N + 1) / 2 * P * sizeof(float));
     A((void **)&g.fix, N * P * sizeof(float));
@@ -197,8 +197,8 @@ hipError_t adjoint_setup(const lll_plan &p, int64_t n_paths, uint64_t seed, hipS
     hipError_t e = launch_precompute(p, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(setup_adjoint_tables_kernel, dim3(p.K), dim3(64), 0, st, d.tenor, d.L0,
-                       d.vol, d.x, d.w, p.N, p.s, p.off, p.nmax, p.alpha, p.beta, p.delta_nig,
-                       gb.xe, gb.dkap, gb.w32, gb.inv_L0);
+                       d.vol, d.gx, d.gw, d.nq, p.N, p.s, p.off, p.nmax, p.alpha, p.beta,
+                       p.delta_nig, gb.xe, gb.dkap, gb.w32, gb.inv_L0);
     e = hipGetLastError();
     g.xe = detail::as_const<float>(gb.xe);
     g.dkap = detail::as_const<float>(gb.dkap);

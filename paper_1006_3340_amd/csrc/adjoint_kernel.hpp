@@ -47,7 +47,7 @@ constexpr int kAdjBlock = 64;  // one wavefront per block: per-lane accumulators
 struct AdjArgs {
     cptr<float> xe;        // [K][Q][nmax]  x_q e^{lambda x_q}
     cptr<float> dkap;      // [K][nmax]     kappa'(lambda) dt
-    cptr<float> w;         // [Q]           quadrature weights
+    cptr<float> w;         // [N][Q]        quadrature weights of each period
     cptr<double> inv_L0;   // [nmax]        1 / L(0, T)
     float *ckpt;           // [N (N+1) / 2][n_paths] live rates at the start of each period
     float *fix;            // [N][n_paths]  X_i at its fixing
@@ -158,8 +158,8 @@ __device__ void forward_lds(const PathArgs<float> &a, const AdjArgs &g, int64_t 
 // start of the step and Xb = adjoint of the state at its end (updated in place
 // to the adjoint at the start).  Parameter adjoints go to the LDS accumulators.
 template <int NMAX, int JC>
-__device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const AdjArgs &g, int k,
-                                             float dH, const float (&X)[NMAX], float (&Xb)[NMAX],
+__device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const AdjArgs &g, int m,
+                                             int k, float dH, const float (&X)[NMAX], float (&Xb)[NMAX],
                                              float *__restrict__ accL0, float *__restrict__ accV) {
     // Cbar = -dt Xbar: the factor -dt is applied once after the node loop
     // (lb and vb below are the adjoints divided by -dt).
@@ -175,9 +175,10 @@ __device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const Adj
     }
     cptr<float> row = a.ew + (size_t)k * kQ * NMAX * 2;
     cptr<float> xrow = g.xe + (size_t)k * kQ * NMAX;
+    const int nq = a.nq[k];
 #pragma unroll 1
-    for (int q = 0; q < kQ; ++q, row += NMAX * 2, xrow += NMAX) {
-        const float W = g.w[q];
+    for (int q = 0; q < nq; ++q, row += NMAX * 2, xrow += NMAX) {
+        const float W = g.w[m * kQ + q];
         P[NMAX - 1] = 1.0f;
 #pragma unroll
         for (int j = NMAX - 2; j >= JC; --j)
@@ -300,7 +301,7 @@ __device__ __forceinline__ void reverse_period(const PathArgs<float> &a, const A
         for (int j = JC; j < NMAX; ++j)
             X[j] = g.scr[(static_cast<int64_t>(js) * NMAX + j) * g.n_paths + gl];
         const float dH = g.scr_dh[static_cast<int64_t>(js) * g.n_paths + gl];
-        reverse_step<NMAX, JC>(a, g, k, dH, X, Xb, accL0, accV);
+        reverse_step<NMAX, JC>(a, g, m, k, dH, X, Xb, accL0, accV);
     }
 }
 

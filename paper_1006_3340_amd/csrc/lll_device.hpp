@@ -1,6 +1,5 @@
 // lll_device.hpp -- device-side building blocks shared by the kernels:
-// the counter-based generator, the driver increment, the NIG cumulant, the
-// scaled Bessel function K_1 and the Gauss-Legendre rule.
+// the counter-based generator, the driver increment and the NIG cumulant.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -185,54 +184,6 @@ __device__ __forceinline__ double nig_cumulant(double u, double alpha, double be
     const double s = sqrt(alpha * alpha - bu * bu);
     const double gs = gamma + s;
     return delta * u * u * (gamma + beta * (2.0 * beta + u) / gs) / (gamma * gs);
-}
-
-// Exponentially scaled K_1(z) e^z from the integral representation
-// K_1(z) = int_0^inf e^{-z cosh t} cosh t dt (Abramowitz & Stegun 9.6.24),
-// by the trapezoidal rule, which converges geometrically in 1/h for this
-// analytic integrand; h = min(1/8, 1/(2 sqrt z)) keeps the error below e^{-60}
-// for all z > 0, and the sum stops once z (cosh t - 1) exceeds 50.
-__device__ inline double bessel_k1e(double z) {
-    const double h = fmin(0.125, 0.5 / sqrt(z));
-    double sum = 0.5;  // t = 0 term counted with weight 1/2
-    for (int j = 1; j < 4000; ++j) {
-        const double t = j * h;
-        const double sh = sinh(0.5 * t);
-        const double e = z * 2.0 * sh * sh;  // z (cosh t - 1)
-        if (e > 50.0) break;
-        sum += exp(-e) * cosh(t);
-    }
-    return h * sum;
-}
-
-// j-th point (ascending) of the n-point Gauss-Legendre rule on [-1, 1] by
-// Newton's method on the three-term recurrence of P_n.
-__device__ inline void gauss_legendre_point(int n, int j, double* x_out, double* w_out) {
-    const double pi = 3.141592653589793238462643383279502884;
-    double x = -cos(pi * (j + 0.75) / (n + 0.5));
-    double dp = 1.0;
-    for (int it = 0; it < 100; ++it) {
-        double p0 = 1.0, p1 = x;
-        for (int k = 2; k <= n; ++k) {
-            const double p2 = ((2.0 * k - 1.0) * x * p1 - (k - 1.0) * p0) / k;
-            p0 = p1;
-            p1 = p2;
-        }
-        dp = n * (x * p1 - p0) / (x * x - 1.0);
-        const double dx = p1 / dp;
-        x -= dx;
-        if (fabs(dx) < 1e-16) break;
-    }
-    // derivative at the converged root for the weight
-    double p0 = 1.0, p1 = x;
-    for (int k = 2; k <= n; ++k) {
-        const double p2 = ((2.0 * k - 1.0) * x * p1 - (k - 1.0) * p0) / k;
-        p0 = p1;
-        p1 = p2;
-    }
-    dp = n * (x * p1 - p0) / (x * x - 1.0);
-    *x_out = x;
-    *w_out = 2.0 / ((1.0 - x * x) * dp * dp);
 }
 
 }  // namespace lll

@@ -27,13 +27,15 @@ struct DeviceTables {
     // FP64 precompute, inspection layout
     double *x = nullptr, *w = nullptr;          // [Q]
     double *kappa = nullptr;                    // [K][N]
-    double *E = nullptr;                        // [K][N][Q]
-    double *b0 = nullptr;                       // [K][N]
+    double *E = nullptr;                        // [K][N][Q], or null: made on demand
+    double *b0 = nullptr;                       // [K][N], written with E
+    double *gx = nullptr, *gw = nullptr;        // [N][Q] the periods' Gauss nodes and weights
+    int *nq = nullptr;                          // [K] node count of each step's period
     double *steps = nullptr;                    // [N][4] per-period increment constants
     double *lam_pm = nullptr;                   // [4] Lambda_+, Lambda_-, moment flag, input flag
     double *vol_base = nullptr;                 // [K][N] the creation vol table (first shifted input)
     // path-kernel layout in the plan's precision (slot columns, nmax wide)
-    void *ew = nullptr;        // [K][Q][nmax][2]  (E, W E)
+    void *ew = nullptr;        // [K][Q][nmax][2]  (E, W E), the first nq[k] node rows
     void *lam = nullptr;       // [K][nmax]
     void *drift0 = nullptr;    // [K][nmax]  -kappa dt
     void *frozen = nullptr;    // [K][nmax]  b0 dt

@@ -212,6 +212,14 @@ int lll_mlp_generate(lll_mlp *m, lll_plan *plan, int64_t n_paths, int records, u
         return fail(LLL_ENOMEM, "training data (%lld pairs): %s", (long long)acc,
                     hipGetErrorString(e));
     }
+    // the labels integrate on the 64 nodes: hold their table for this call
+    const bool held = plan->d.E != nullptr;
+    if (!held) e = hipMalloc(&plan->d.E, sizeof(double) * plan->K * plan->N * lll::kQSize);
+    if (e != hipSuccess) {
+        plan->d.E = nullptr;
+        free_data(m);
+        return fail(LLL_ENOMEM, "table E: %s", hipGetErrorString(e));
+    }
     e = hipMemcpyAsync(m->poff_dev, m->poff.data(), sizeof(int64_t) * (m->n_states + 1),
                        hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = lll::launch_precompute(*plan, st);
@@ -223,7 +231,12 @@ int lll_mlp_generate(lll_mlp *m, lll_plan *plan, int64_t n_paths, int records, u
     if (e == hipSuccess)
         e = hipMemcpyAsync(m->info_host, m->info, sizeof(float) * (2 * kRates + 1),
                            hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const hipError_t done = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = done;
+    if (!held) {
+        (void)hipFree(plan->d.E);
+        plan->d.E = nullptr;
+    }
     if (e != hipSuccess) {
         free_data(m);
         return hip_fail(e, "generating training pairs");

@@ -25,7 +25,7 @@
 // Nothing is shared between wavefronts inside the step loop.
 //
 // Fallback: a path whose later-rate state leaves the range seen in training
-// (per rate) takes the 64-node quadrature coupling for that rate instead.
+// (per rate) takes the quadrature coupling for that rate instead.
 // Judge: every judge_stride-th wavefront also evaluates the quadrature at every
 // step and records the surrogate's absolute and relative drift errors.
 #include <hip/hip_runtime.h>
@@ -131,7 +131,8 @@ __device__ __forceinline__ void finish_step(const PathArgs<float> &a, int k, flo
         float ell[kSlots], Cq[kSlots];
 #pragma unroll
         for (int j = J0; j < kSlots; ++j) ell[j] = detail::ell_of(X[j], a.cinv[j]);
-        detail::quad_coupling<float, kSlots, J0>(a.ew + (size_t)k * kQ * kSlots * 2, ell, Cq);
+        detail::quad_coupling<float, kSlots, J0>(a.ew + (size_t)k * kQ * kSlots * 2, a.nq[k], ell,
+                                                    Cq);
 #pragma unroll
         for (int j = J0; j < kSlots; ++j) {
             if (judge) {

@@ -33,8 +33,11 @@ namespace {
 
 constexpr size_t kScratchBytes = LLL_STATIC_WORKSPACE_BYTES;
 constexpr int kMaxDevices = 64;
+// the periods' Gauss nodes and weights lie behind the workspace proper, so the
+// passes that fit it do not depend on them
+constexpr size_t kRuleBytes = 2 * LLL_N_MAX * kQSize * sizeof(double);
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kRuleBytes];
 
 std::mutex g_scratch_mu;
 void *g_scratch_dev[kMaxDevices] = {};
@@ -78,7 +81,11 @@ size_t carve(lll_plan &p, unsigned char *base, int64_t n_paths, bool first_order
     auto R = [&](void **ptr, size_t n) { *ptr = take(n * esz); };
     DeviceTables &d = p.d;
     D(&d.tenor, N); D(&d.delta, N); D(&d.L0, N); D(&d.vol, K * N); D(&d.strikes, N * S);
-    D(&d.x, Q); D(&d.w, Q); D(&d.kappa, K * N); D(&d.E, K * N * Q); D(&d.b0, K * N);
+    D(&d.x, Q); D(&d.w, Q); D(&d.kappa, K * N);
+    // the room of the 64-node table E, which this pass does not make, takes the
+    // node counts
+    d.nq = reinterpret_cast<int *>(take(K * N * Q * sizeof(double)));
+    D(&d.b0, K * N);
     D(&d.steps, 4 * N); D(&d.lam_pm, 4);
     R(&d.ew, K * Q * NM * 2); R(&d.lam, K * NM); R(&d.drift0, K * NM); R(&d.frozen, K * NM);
     R(&d.dt, K); R(&d.cinv, NM);
@@ -88,6 +95,10 @@ size_t carve(lll_plan &p, unsigned char *base, int64_t n_paths, bool first_order
     D(&d.chunks, chunks * N * nstat);
     D(&d.sums, N * nstat);
     D(&d.results, 3 * N * S + 2 * N);
+    if (base) {
+        d.gx = reinterpret_cast<double *>(base + kScratchBytes);
+        d.gw = d.gx + LLL_N_MAX * kQSize;
+    }
     return at;
 }
 

@@ -49,6 +49,7 @@ __host__ __device__ inline cptr<T> as_const(const T *p) {
 template <typename Real>
 struct PathArgs {
     cptr<Real> ew;         // [K][Q][nmax][2]
+    cptr<int> nq;          // [K] nodes of step k's rule (rows of ew[k])
     cptr<Real> lam;        // [K][nmax]
     cptr<Real> drift0;     // [K][nmax]
     cptr<Real> frozen;     // [K][nmax]
@@ -94,14 +95,14 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Coupling sums C[j], j = J0 .. nmax-2, of the jump drift for the live slots
-// J0 .. nmax-1 at step k (row = table of step k).  C[nmax-1] = 0.
+// J0 .. nmax-1 at step k (row = table of step k, nq nodes).  C[nmax-1] = 0.
 template <typename Real, int NMAX, int J0>
-__device__ __forceinline__ void quad_coupling(cptr<Real> row, const Real (&ell)[NMAX],
+__device__ __forceinline__ void quad_coupling(cptr<Real> row, int nq, const Real (&ell)[NMAX],
                                               Real (&C)[NMAX]) {
 #pragma unroll
     for (int j = J0; j < NMAX; ++j) C[j] = Real(0);
     if constexpr (J0 < NMAX - 1) {
-        for (int q = 0; q < kQ; ++q, row += NMAX * 2) {
+        for (int q = 0; q < nq; ++q, row += NMAX * 2) {
             Real R = ell[NMAX - 1] * row[2 * (NMAX - 1)];
 #pragma unroll
             for (int j = NMAX - 2; j >= J0; --j) {
@@ -145,16 +146,16 @@ __device__ __forceinline__ void first_order_coupling(cptr<Real> k2k, const Real 
 // Second-order expansion of the coupling (Section 3.2, eq. (drifta2)): the
 // product prod_{l>i}(1 + ell_l E_l) truncated after its terms of degree 2 in
 // ell, e1 + e2 (elementary symmetric sums of the ell_l E_l, l > i), integrated
-// with the same 64-node rule.  Per node, from the top slot down, with
+// with the same rule.  Per node, from the top slot down, with
 // u = 1 + e1 and s = e1 + e2 of the slots above j:
 //     C_j += W E_j s,   t = ell_j E_j,   s += t u,   u += t.
 template <typename Real, int NMAX, int J0>
-__device__ __forceinline__ void quad_coupling2(cptr<Real> row, const Real (&ell)[NMAX],
+__device__ __forceinline__ void quad_coupling2(cptr<Real> row, int nq, const Real (&ell)[NMAX],
                                                Real (&C)[NMAX]) {
 #pragma unroll
     for (int j = J0; j < NMAX; ++j) C[j] = Real(0);
     if constexpr (J0 < NMAX - 1) {
-        for (int q = 0; q < kQ; ++q, row += NMAX * 2) {
+        for (int q = 0; q < nq; ++q, row += NMAX * 2) {
             Real t = ell[NMAX - 1] * row[2 * (NMAX - 1)];
             Real s = t;
             Real u = Real(1) + t;
@@ -175,7 +176,7 @@ __device__ __forceinline__ void quad_coupling2(cptr<Real> row, const Real (&ell)
 
 // Coupling sums of the scheme: the first-order expansion, the Brownian
 // closed form (exact, hence also the second-order expansion), the truncated
-// product or the full product on the 64-node rule.
+// product or the full product on the step's rule.
 template <typename Real, int NMAX, int SCHEME, int J0>
 __device__ __forceinline__ void coupling(const PathArgs<Real> &a, int k, const Real (&ell)[NMAX],
                                          Real (&C)[NMAX]) {
@@ -184,9 +185,9 @@ __device__ __forceinline__ void coupling(const PathArgs<Real> &a, int k, const R
     else if (a.brownian)
         brownian_coupling<Real, NMAX, J0>(a.lam + (size_t)k * NMAX, static_cast<Real>(a.c), ell, C);
     else if constexpr (SCHEME == kSecond)
-        quad_coupling2<Real, NMAX, J0>(a.ew + (size_t)k * kQ * NMAX * 2, ell, C);
+        quad_coupling2<Real, NMAX, J0>(a.ew + (size_t)k * kQ * NMAX * 2, a.nq[k], ell, C);
     else
-        quad_coupling<Real, NMAX, J0>(a.ew + (size_t)k * kQ * NMAX * 2, ell, C);
+        quad_coupling<Real, NMAX, J0>(a.ew + (size_t)k * kQ * NMAX * 2, a.nq[k], ell, C);
 }
 
 // PICARD's predictor (the frozen-drift path, paper Section 3.1) enters the
@@ -560,7 +561,7 @@ __device__ void drift_one(const PathArgs<Real> &a, int k, const double *__restri
     if (a.brownian)
         brownian_coupling<Real, NMAX, J0>(a.lam + (size_t)k * NMAX, static_cast<Real>(a.c), ell, C);
     else
-        quad_coupling<Real, NMAX, J0>(a.ew + (size_t)k * kQ * NMAX * 2, ell, C);
+        quad_coupling<Real, NMAX, J0>(a.ew + (size_t)k * kQ * NMAX * 2, a.nq[k], ell, C);
 #pragma unroll
     for (int j = J0; j < NMAX; ++j) {
         const int r = j - a.off;
@@ -593,6 +594,7 @@ inline PathArgs<Real> make_args(const lll_plan &p, uint64_t seed, int64_t n_path
     const DeviceTables &d = p.d;
     PathArgs<Real> a;
     a.ew = as_const(static_cast<const Real *>(d.ew));
+    a.nq = as_const<int>(d.nq);
     a.lam = as_const(static_cast<const Real *>(d.lam));
     a.drift0 = as_const(static_cast<const Real *>(d.drift0));
     a.frozen = as_const(static_cast<const Real *>(d.frozen));

@@ -481,6 +481,8 @@ hipError_t picard_mp_alloc(lll_plan &p) {
     const int64_t chunk = picard_mp_chunk(p);
     const size_t G = (size_t)chunk / kGroup;
     hipError_t e = hipMalloc(&p.d.mp_ewq, (size_t)p.K * p.N * kQ * sizeof(float2));
+    if (e == hipSuccess && !p.d.E)
+        e = hipMalloc(&p.d.E, (size_t)p.K * p.N * kQ * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&p.d.mp_ell, G * ell_entries(p.s, p.N) * kGroup * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&p.d.mp_z, G * z_entries(p.N) * kGroup * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&p.d.mp_pay, (size_t)chunk * p.N * (p.S + 1) * sizeof(double));

@@ -11,7 +11,8 @@
 // X_+ = min(36 / (alpha - beta - Lambda_+), 40), X_- = min(36 / (alpha + beta - Lambda_-), 40)
 // where Lambda_pm bounds the sum of the live vols' positive / negative parts.
 //
-// Tables (per step k and live rate slot j):
+// Tables (per step k and live rate slot j), at the nodes x_q of the period's
+// Gauss rule (see setup_rule_kernel):
 //   E[k][q][j]  = e^{lambda_{k,j} x_q} - 1 and W_q E   (path kernel, interleaved)
 //   drift0      = -kappa(lambda_{k,j}) dt_k
 //   frozen      = b0 dt_k, b0 the drift at the initial rates (eq. (Picard-2))
@@ -24,178 +25,416 @@
 namespace lll {
 namespace {
 
-__device__ double levy_density(double x, double alpha, double beta, double delta) {
-    const double pi = 3.141592653589793238462643383279502884;
-    const double ax = fabs(x);
-    return delta * alpha / pi * exp(beta * x - alpha * ax) * bessel_k1e(alpha * ax) / ax;
+// Positive points (descending) and weights of the 32-point Gauss-Legendre rule
+// on [-1, 1] (roots of P_32 and 2 / ((1 - x^2) P_32'(x)^2), from 40-digit
+// arithmetic).
+__device__ const double kGLx[kGL / 2] = {
+    0.9972638618494815635, 0.9856115115452683354, 0.9647622555875064308, 0.9349060759377396892,
+    0.896321155766052124, 0.8493676137325699701, 0.794483795967942407, 0.7321821187402896804,
+    0.663044266930215201, 0.587715757240762329, 0.50689990893222939, 0.4213512761306353454,
+    0.3318686022821276498, 0.2392873622521370745, 0.1444719615827964935, 0.04830766568773831623};
+__device__ const double kGLw[kGL / 2] = {
+    0.0070186100094700966, 0.01627439473090567061, 0.02539206530926205946, 0.0342738629130214331,
+    0.04283589802222668066, 0.0509980592623761762, 0.05868409347853554715, 0.06582222277636184684,
+    0.07234579410884850623, 0.07819389578707030647, 0.08331192422694675522, 0.08765209300440381114,
+    0.09117387869576388471, 0.09384439908080456564, 0.09563872007927485942, 0.09654008851472780057};
+
+// v of lane i + its DPP image, for the FP64 wavefront sum below.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(u), CTRL, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(u >> 32), CTRL, 0xF, 0xF, true);
+    return v + __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-// One block of 64 threads: quadrature rule, Lambda_pm, per-period increment
-// constants and per-slot constants.
+__device__ __forceinline__ double lane_of(double v, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), lane);
+    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// Wavefront sum in every lane: within each row of 16 lanes by DPP (quad
+// permutes, half-row and row mirror), then the four rows through scalar
+// registers.  The rule's set-up is a chain of such sums, and a DPP step takes a
+// tenth of a cross-lane LDS permute's latency.
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+    v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+}
+
+// The step tables do not hold the 64-node rule itself but, per period, the
+// n-point Gauss rule of the same discrete measure, n as small as the plan's
+// precision allows.  With p_U the probability that independent Bernoulli(ell_l)
+// variables select the subset U of the later rates,
+//     prod_{l>i} (1 + ell_l E_l) = sum_U p_U e^{lambda_U x},   lambda_U = sum_{l in U} lambda_l,
+// so the coupling is an average of the functions
+//     f_{lambda,a}(x) = (e^{lambda x} - 1)(e^{a x} - 1),   lambda = lambda_i, a = lambda_U,
+// with a between -Lambda_- and Lambda_+ of the live rates: x^2 e^{theta x} times
+// an entire function of exponential type at most about (Lambda_+ + Lambda_-) / 2
+// for a tilt theta near (Lambda_+ - Lambda_-) / 2, and the Gauss rule of the tilted
+// measure sum_q W_q x_q^2 e^{theta x_q} delta_{x_q} converges geometrically on them
+// (error down 50 to 500 times per added node at the light-tailed structures; a
+// factor of 0.45 instead of 0.5 balances its ends, halving the largest error).
+// f keeps one sign in x, so an error relative to the 64-node sum of f that holds
+// at every a bounds the error of every coupling relative to itself, whatever the
+// state.  It is largest at the ends of the range of a: each candidate is checked
+// against the 64-node sums at a = Lambda_+, at -Lambda_- and in the limit a -> 0
+// (f / a -> (e^{lambda x} - 1) x), for the smallest and largest live vol, before it
+// is taken:
+//   FP32 plans: 2^-30, a 64th of a unit in the last place of the tables;
+//   FP64 plans: 2^-47, the rounding of the 64-term sums.
+// At 64 nodes FULL spent 15.3 of its 19.1 ms (20 rates, 2^20 paths) in the
+// recursion; 4 to 6 nodes suffice there (6 at 40 rates, 8 at 60), 8 to 16 with
+// the tails of alpha = 1.5, and near the moment limit, where none of the
+// candidates passes, the period keeps the 64 nodes.
+constexpr int kCand[] = {3, 4, 5, 6, 7, 8, 10, 12, 16, 24};
+constexpr int kNCand = sizeof(kCand) / sizeof(kCand[0]);
+constexpr int kGaussMax = 24;
+constexpr int kRuleBlock = 64 * kNCand;
+constexpr double kTolF32 = 9.3132257461547852e-10;   // 2^-30
+constexpr double kTolF64 = 7.1054273576010019e-15;   // 2^-47
+
+// The test functions of the acceptance check at one point, times the weight:
+// lambda the smallest (l0) and the largest (l1) live vol of the period, a the
+// largest positive (ap) and negative (am) subset sum and the limit a -> 0.
+struct TestVols {
+    double l0, l1, ap, am;
+};
+constexpr int kTests = 6;
+__device__ __forceinline__ void add_tests(const TestVols &t, double x, double w,
+                                          double (&f)[kTests]) {
+    const double e0 = w * expm1(t.l0 * x), e1 = w * expm1(t.l1 * x);
+    const double gp = expm1(t.ap * x), gm = t.am < 0.0 ? expm1(t.am * x) : 0.0;
+    f[0] = e0 * gp;
+    f[1] = e1 * gp;
+    f[2] = e0 * gm;
+    f[3] = e1 * gm;
+    f[4] = e0 * x;
+    f[5] = e1 * x;
+}
+
+// One block per accrual period m, one wavefront per candidate node count.  Every
+// block forms the 64-node rule (block 0 also writes it, with Lambda_pm and the
+// per-period and per-slot constants), then its period's Gauss rule.
+// Latency-bound: one launch of N blocks.  The 64 Bessel values are summed by
+// several lanes each and Lambda_pm by 8 lanes a step, and the Gauss-Legendre points
+// are tabulated: with one block of 64 threads iterating for them the rule alone
+// took 85-220 us of every pass.
 template <typename Real>
-__global__ void __launch_bounds__(64) setup_rule_kernel(
+__global__ void __launch_bounds__(kRuleBlock) setup_rule_kernel(
     const double *__restrict__ tenor, const double *__restrict__ delta,
     const double *__restrict__ L0, const double *__restrict__ vol, int N, int s, int off,
     int driver, double alpha, double beta, double delta_nig, double c, double *__restrict__ x_out,
     double *__restrict__ w_out, double *__restrict__ steps, double *__restrict__ lam_pm,
-    Real *__restrict__ cinv, double *__restrict__ L0s, double *__restrict__ deltas, int nmax) {
-    __shared__ double red_p[64], red_m[64];
-    const int t = threadIdx.x;
+    Real *__restrict__ cinv, double *__restrict__ L0s, double *__restrict__ deltas, int nmax,
+    double *__restrict__ gx, double *__restrict__ gw, int *__restrict__ nq) {
+    constexpr int kWaves = kRuleBlock / 64;
+    __shared__ double red[6][kWaves];
+    __shared__ double xs[kQ], ws[kQ];
+    __shared__ double ja[kGaussMax], jb[kGaussMax], mu0s;
+    __shared__ int ok[kWaves];
+    const int t = threadIdx.x, lane = t % 64, wave = t / 64;
     const int K = N * s;
-    double lp = 0.0, lm = 0.0;
+    const int m = blockIdx.x;
+
+    // Lambda_pm over all steps, and over this period with its extreme live vols
+    double lp = 0.0, lm = 0.0, mp = 0.0, mm = 0.0, vmin = 1e300, vmax = -1e300;
     int bad = 0;  // inputs the host could not check (set from device memory)
-    for (int k = t; k < K; k += 64) {
-        const int m = k / s;
+    const int sub = t % 8;
+    for (int k0 = 0; k0 < K; k0 += kRuleBlock / 8) {
+        const int k = k0 + t / 8;
+        const int first = k / s;
         double sp = 0.0, sm = 0.0;
-        for (int r = m; r < N; ++r) {
-            const double v = vol[(size_t)k * N + r];
-            bad |= !isfinite(v);
-            sp += fmax(v, 0.0);
-            sm += fmax(-v, 0.0);
-        }
+        if (k < K)
+            for (int r = sub; r < N; r += 8) {
+                if (r < first) continue;
+                const double v = vol[(size_t)k * N + r];
+                bad |= !isfinite(v);
+                sp += fmax(v, 0.0);
+                sm += fmax(-v, 0.0);
+                if (first == m) {
+                    vmin = fmin(vmin, v);
+                    vmax = fmax(vmax, v);
+                }
+            }
+        sp = dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(sp)));
+        sm = dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(sm)));
         lp = fmax(lp, sp);
         lm = fmax(lm, sm);
-    }
-    for (int r = t; r < N; r += 64) bad |= !(L0[r] > 0.0) || !isfinite(L0[r]);
-    bad = __syncthreads_or(bad);
-    red_p[t] = lp;
-    red_m[t] = lm;
-    __syncthreads();
-    for (int o = 32; o > 0; o >>= 1) {
-        if (t < o) {
-            red_p[t] = fmax(red_p[t], red_p[t + o]);
-            red_m[t] = fmax(red_m[t], red_m[t + o]);
+        if (first == m) {
+            mp = fmax(mp, sp);
+            mm = fmax(mm, sm);
         }
-        __syncthreads();
     }
-    const double Lp = red_p[0], Lm = red_m[0];
-    if (t == 0) {
-        lam_pm[0] = Lp;
-        lam_pm[1] = Lm;
-        // (LR1): the drift integral is finite iff Lambda_+ < alpha - beta and
-        // Lambda_- < alpha + beta; the pricing pass returns NaN otherwise
-        lam_pm[2] = (driver == kNig && !(Lp < alpha - beta && Lm < alpha + beta)) ? 1.0 : 0.0;
-        lam_pm[3] = bad ? 1.0 : 0.0;
+    for (int r = t; r < N; r += kRuleBlock) bad |= !(L0[r] > 0.0) || !isfinite(L0[r]);
+    bad = __syncthreads_or(bad);
+    double v6[6] = {lp, lm, mp, mm, -vmin, vmax};
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v6[i] = fmax(v6[i], __shfl_xor(v6[i], o, 64));
+        if (lane == 0) red[i][wave] = v6[i];
     }
-    if (driver == kNig) {
-        const double xp = fmin(kTailExponent / (alpha - beta - Lp), kXCap);
-        const double xm = fmin(kTailExponent / (alpha + beta - Lm), kXCap);
-        const int j = t % kGL;
-        const bool right = t < kGL;
-        double g, wg;
-        gauss_legendre_point(kGL, j, &g, &wg);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        v6[i] = red[i][0];
+        for (int w = 1; w < kWaves; ++w) v6[i] = fmax(v6[i], red[i][w]);
+    }
+    const double Lp = v6[0], Lm = v6[1];
+
+    if (blockIdx.x == 0) {
+        if (t == 0) {
+            lam_pm[0] = Lp;
+            lam_pm[1] = Lm;
+            // (LR1): the drift integral is finite iff Lambda_+ < alpha - beta and
+            // Lambda_- < alpha + beta; the pricing pass returns NaN otherwise
+            lam_pm[2] = (driver == kNig && !(Lp < alpha - beta && Lm < alpha + beta)) ? 1.0 : 0.0;
+            lam_pm[3] = bad ? 1.0 : 0.0;
+        }
+        if (t < N) {
+            const double Ta = (t == 0) ? 0.0 : tenor[t - 1];
+            const double dt = (tenor[t] - Ta) / s;
+            double *sc = steps + 4 * t;
+            if (driver == kNig) {
+                const double gamma = sqrt(alpha * alpha - beta * beta);
+                sc[0] = delta_nig * dt / gamma;                 // IG mean
+                sc[1] = (delta_nig * dt) * (delta_nig * dt);    // IG shape
+                sc[2] = -delta_nig * beta / gamma * dt;         // mu_H dt
+                sc[3] = 0.0;
+            } else {
+                sc[0] = sc[1] = sc[2] = 0.0;
+                sc[3] = sqrt(c * dt);
+            }
+        }
+        if (t < nmax) {
+            const int r = t - off;
+            if (r >= 0) {
+                cinv[t] = static_cast<Real>(1.0 / (delta[r] * L0[r]));
+                L0s[t] = L0[r];
+                deltas[t] = delta[r];
+            } else {
+                cinv[t] = Real(0);
+                L0s[t] = 0.0;
+                deltas[t] = 0.0;
+            }
+        }
+    }
+    if (driver != kNig) {  // the Brownian coupling is closed form: no nodes
+        if (t < kQ) {
+            gx[m * kQ + t] = gw[m * kQ + t] = 0.0;
+            if (m == 0) x_out[t] = w_out[t] = 0.0;
+        }
+        for (int i = t; i < s; i += kRuleBlock) nq[m * s + i] = kQ;
+        return;
+    }
+
+    // The 64-node rule; 8 lanes share each node's Bessel sum
+    // K_1(z) e^z = int_0^inf e^{-z (cosh u - 1)} cosh u du (Abramowitz & Stegun
+    // 9.6.24) by the trapezoidal rule, which converges geometrically for this
+    // analytic integrand: step h = min(1/8, 1 / (2 sqrt z)), error below e^{-60}
+    // for all z > 0, cut where z (cosh u - 1) > 50.
+    const double xp = fmin(kTailExponent / (alpha - beta - Lp), kXCap);
+    const double xm = fmin(kTailExponent / (alpha + beta - Lm), kXCap);
+    if (t < 8 * kQ) {
+        const int q = t / 8, j = q % kGL;
+        const bool right = q < kGL;
+        const double g = j < kGL / 2 ? -kGLx[j] : kGLx[kGL - 1 - j];
+        const double wg = kGLw[j < kGL / 2 ? j : kGL - 1 - j];
         const double v = 0.5 * (g + 1.0);
-        const double wv = 0.5 * wg;
         const double X = right ? xp : xm;
         const double xq = right ? X * v * v : -X * v * v;
-        x_out[t] = xq;
-        w_out[t] = wv * 2.0 * X * v * levy_density(xq, alpha, beta, delta_nig);
-    } else {
-        x_out[t] = 0.0;
-        w_out[t] = 0.0;
-    }
-    if (t < N) {
-        const double Ta = (t == 0) ? 0.0 : tenor[t - 1];
-        const double dt = (tenor[t] - Ta) / s;
-        double *sc = steps + 4 * t;
-        if (driver == kNig) {
-            const double gamma = sqrt(alpha * alpha - beta * beta);
-            sc[0] = delta_nig * dt / gamma;                 // IG mean
-            sc[1] = (delta_nig * dt) * (delta_nig * dt);    // IG shape
-            sc[2] = -delta_nig * beta / gamma * dt;         // mu_H dt
-            sc[3] = 0.0;
-        } else {
-            sc[0] = sc[1] = sc[2] = 0.0;
-            sc[3] = sqrt(c * dt);
+        const double ax = fabs(xq), z = alpha * ax;
+        const double h = fmin(0.125, 0.5 / sqrt(z));
+        double sum = sub == 0 ? 0.5 : 0.0;  // the u = 0 term counts half
+        for (int i = sub == 0 ? 8 : sub; i < 4000; i += 8) {
+            const double em = expm1(0.5 * i * h);
+            const double sh = 0.5 * (em + em / (1.0 + em));  // sinh(u / 2)
+            const double e = 2.0 * sh * sh;                  // cosh u - 1
+            if (!(z * e <= 50.0)) break;
+            sum += exp(-z * e) * (1.0 + e);
+        }
+        sum = dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(sum)));
+        if (sub == 0) {
+            const double pi = 3.141592653589793238462643383279502884;
+            xs[q] = xq;
+            ws[q] = 0.5 * wg * 2.0 * X * v *
+                    (delta_nig * alpha / pi * exp(beta * xq - z) * (h * sum) / ax);
         }
     }
-    if (t < nmax) {
-        const int r = t - off;
-        if (r >= 0) {
-            cinv[t] = static_cast<Real>(1.0 / (delta[r] * L0[r]));
-            L0s[t] = L0[r];
-            deltas[t] = delta[r];
-        } else {
-            cinv[t] = Real(0);
-            L0s[t] = 0.0;
-            deltas[t] = 0.0;
+    __syncthreads();
+    const double xq = xs[lane], wq = ws[lane];
+    if (m == 0 && wave == 0) {
+        x_out[lane] = xq;
+        w_out[lane] = wq;
+    }
+
+    // Jacobi matrix (ja diagonal, jb squared off-diagonal) of the tilted measure
+    // by the Stieltjes procedure, lane = node
+    const double Mp = v6[2], Mm = v6[3];
+    const double theta = 0.45 * (Mp - Mm);
+    const double tilt = exp(theta * xq);
+    if (wave == 0) {
+        const double nu = wq * xq * xq * tilt;
+        const double mu0 = wave_sum_dpp(nu);
+        if (lane == 0) mu0s = mu0;
+        double prev = 0.0, cur = sqrt(nu / mu0), b = 0.0;
+        for (int j = 0; j < kGaussMax; ++j) {
+            const double a = wave_sum_dpp(cur * cur * xq);
+            const double r = (xq - a) * cur - b * prev;
+            const double b2 = wave_sum_dpp(r * r);
+            if (lane == 0) {
+                ja[j] = a;
+                jb[j] = b2;
+            }
+            b = sqrt(b2);
+            prev = cur;
+            cur = b > 0.0 ? r / b : 0.0;
         }
     }
+    __syncthreads();
+
+    // This wavefront's candidate: lane i < n finds the i-th node, bisection on the
+    // sign changes of the monic polynomials p_{j+1} = (x - a_j) p_j - b_j^2 p_{j-1}
+    // (their number is the number of nodes above x), then Newton steps
+    const int n = kCand[wave];
+    double lo = -xm, hi = xp;
+    for (int it = 0; it < 26; ++it) {
+        const double x = 0.5 * (lo + hi);
+        double p0 = 1.0, p1 = x - ja[0];
+        int above = p1 < 0.0;
+        for (int j = 1; j < n; ++j) {
+            const double p2 = fma(x - ja[j], p1, -jb[j - 1] * p0);
+            above += (p2 < 0.0) != (p1 < 0.0);
+            p0 = p1;
+            p1 = p2;
+        }
+        if (n - above > lane) hi = x;
+        else lo = x;
+    }
+    double x = 0.5 * (lo + hi);
+    for (int it = 0; it < 4; ++it) {
+        double p0 = 1.0, p1 = x - ja[0], d0 = 0.0, d1 = 1.0;
+        for (int j = 1; j < n; ++j) {
+            const double p2 = fma(x - ja[j], p1, -jb[j - 1] * p0);
+            const double d2 = fma(x - ja[j], d1, fma(-jb[j - 1], d0, p1));
+            p0 = p1;
+            p1 = p2;
+            d0 = d1;
+            d1 = d2;
+        }
+        const double step = p1 / d1;
+        if (fabs(step) <= hi - lo) x -= step;
+    }
+    // weight mu_0 / sum_j p_j(x)^2 / |p_j|^2, then back from the tilted measure;
+    // a node at the origin itself (where x^2 vanishes) moves off it
+    double wt = 0.0;
+    {
+        double p0 = 0.0, p1 = 1.0, nrm = 1.0, sum = 1.0;
+        for (int j = 0; j + 1 < n; ++j) {
+            const double p2 = fma(x - ja[j], p1, -(j ? jb[j - 1] : 0.0) * p0);
+            p0 = p1;
+            p1 = p2;
+            nrm *= jb[j];
+            sum += p1 * p1 / nrm;
+        }
+        if (fabs(x) < 1e-12) x = 1e-12;
+        wt = mu0s / sum / (x * x * exp(theta * x));
+    }
+    const TestVols tv{-v6[4], v6[5], Mp, -Mm};
+    double ref[kTests], got[kTests] = {};
+    add_tests(tv, xq, wq, ref);
+    if (lane < n) add_tests(tv, x, wt, got);
+    bool pass = lane >= n || isfinite(wt);
+    const double tol = sizeof(Real) == 4 ? kTolF32 : kTolF64;
+#pragma unroll
+    for (int i = 0; i < kTests; ++i) {
+        const double fr = wave_sum_dpp(ref[i]), fg = wave_sum_dpp(got[i]);
+        pass = pass && fabs(fg - fr) <= tol * fabs(fr);
+    }
+    pass = __all(pass);
+    if (lane == 0) ok[wave] = pass;
+    __syncthreads();
+    int pick = 0;
+    while (pick < kNCand && !ok[pick]) ++pick;
+    if (pick == wave) {
+        if (lane < n) {
+            gx[m * kQ + lane] = x;
+            gw[m * kQ + lane] = wt;
+        }
+    } else if (pick == kNCand && wave == 0) {
+        gx[m * kQ + lane] = xq;
+        gw[m * kQ + lane] = wq;
+    }
+    for (int i = t; i < s; i += kRuleBlock) nq[m * s + i] = pick < kNCand ? kCand[pick] : kQ;
 }
 
-// One block of 64 threads (one per node q) per Euler step k.
+// One block of 256 threads per Euler step k: the cumulants, the tables
+// (E, W E) at the period's nodes, and the frozen drift.
 template <typename Real>
-__global__ void __launch_bounds__(64) setup_tables_kernel(
+__global__ void __launch_bounds__(256) setup_tables_kernel(
     const double *__restrict__ tenor, const double *__restrict__ delta,
     const double *__restrict__ L0, const double *__restrict__ vol,
-    const double *__restrict__ x_in, const double *__restrict__ w_in, int N, int s, int off,
-    int nmax, int driver, double alpha, double beta, double delta_nig, double c,
-    double *__restrict__ kappa_out, double *__restrict__ E_out, double *__restrict__ b0_out,
-    Real *__restrict__ ew, Real *__restrict__ lam_t, Real *__restrict__ drift0,
-    Real *__restrict__ frozen, Real *__restrict__ dt_t) {
-    __shared__ double cq[LLL_N_MAX_MP][kQ];    // WE_q R_q contributions per rate
+    const double *__restrict__ gx, const double *__restrict__ gw, const int *__restrict__ nq_in,
+    int N, int s, int off, int nmax, int driver, double alpha, double beta, double delta_nig,
+    double c, double *__restrict__ kappa_out, Real *__restrict__ ew, Real *__restrict__ lam_t,
+    Real *__restrict__ drift0, Real *__restrict__ frozen, Real *__restrict__ dt_t) {
+    __shared__ double es[LLL_N_MAX_MP * kQ];   // E, then W E R, by [rate][node]
     __shared__ double kap[LLL_N_MAX_MP];
-    const int k = blockIdx.x;
-    const int q = threadIdx.x;
+    const int k = blockIdx.x, t = threadIdx.x;
     const int m = k / s;
     const double Ta = (m == 0) ? 0.0 : tenor[m - 1];
     const double dt = (tenor[m] - Ta) / s;
     const double *lam = vol + (size_t)k * N;
-    const double xq = x_in[q], wq = w_in[q];
     const bool nig = (driver == kNig);
+    const int nq = nq_in[k];
+    const double *x = gx + m * kQ, *w = gw + m * kQ;
 
-    // cumulant of every live rate
-    if (q < N) {
+    if (t < N) {  // cumulant of every live rate
         double kv = 0.0;
-        if (q >= m) {
-            const double u = lam[q];
+        if (t >= m) {
+            const double u = lam[t];
             kv = nig ? nig_cumulant(u, alpha, beta, delta_nig) : 0.5 * c * u * u;
         }
-        kap[q] = kv;
-        kappa_out[(size_t)k * N + q] = kv;
+        kap[t] = kv;
+        kappa_out[(size_t)k * N + t] = kv;
     }
-    __syncthreads();
-
-    // quadrature tables and the suffix recursion at the initial rates:
-    // R <- R + ell0_l E_l (1 + R) from the last rate down, C_i = sum_q W E_i R_q
-    double R = 0.0;
-    for (int r = N - 1; r >= 0; --r) {
-        const int j = r + off;
+    for (int i = t; i < nmax * nq; i += 256) {
+        const int q = i / nmax, j = i % nmax, r = j - off;
+        const double E = (r >= m && nig) ? expm1(lam[r] * x[q]) : 0.0;
         Real *row = ew + (((size_t)k * kQ + q) * nmax + j) * 2;
-        if (r >= m && nig) {
-            const double E = expm1(lam[r] * xq);
-            const double WE = wq * E;
-            E_out[((size_t)k * N + r) * kQ + q] = E;
-            row[0] = static_cast<Real>(E);
-            row[1] = static_cast<Real>(WE);
-            cq[r][q] = WE * R;
-            const double ell0 = delta[r] * L0[r] / (1.0 + delta[r] * L0[r]);
-            R = R + ell0 * E * (1.0 + R);
-        } else {
-            E_out[((size_t)k * N + r) * kQ + q] = 0.0;
-            row[0] = Real(0);
-            row[1] = Real(0);
-            cq[r][q] = 0.0;
-        }
+        row[0] = static_cast<Real>(E);
+        row[1] = static_cast<Real>(w[q] * E);
+        if (r >= 0) es[r * kQ + q] = E;
     }
-    for (int j = q; j < off; j += kQ) {  // unused leading slots
-        Real *row = ew + (((size_t)k * kQ) * nmax + j) * 2;
-        for (int qq = 0; qq < kQ; ++qq) {
-            row[(size_t)qq * nmax * 2] = Real(0);
-            row[(size_t)qq * nmax * 2 + 1] = Real(0);
+    __syncthreads();
+    // suffix recursion at the initial rates: R <- R + ell0_l E_l (1 + R) from the
+    // last rate down, C_i = sum_q W E_i R_q
+    if (t < nq) {
+        double R = 0.0;
+        for (int r = N - 1; r >= m; --r) {
+            const double E = es[r * kQ + t];
+            const double ell0 = delta[r] * L0[r] / (1.0 + delta[r] * L0[r]);
+            es[r * kQ + t] = w[t] * E * R;
+            R = R + ell0 * E * (1.0 + R);
         }
     }
     __syncthreads();
-    if (q == 0) dt_t[k] = static_cast<Real>(dt);
-    if (q < nmax) {
-        const int j = q, r = j - off;
+    if (t == 0) dt_t[k] = static_cast<Real>(dt);
+    if (t < nmax) {
+        const int j = t, r = j - off;
         double b0 = 0.0, kv = 0.0, lv = 0.0;
         if (r >= m) {
             kv = kap[r];
             lv = lam[r];
             double C = 0.0;
             if (nig) {
-                for (int qq = 0; qq < kQ; ++qq) C += cq[r][qq];
+                for (int q = 0; q < nq; ++q) C += es[r * kQ + q];
             } else {
                 double S = 0.0;
                 for (int l = r + 1; l < N; ++l)
@@ -204,27 +443,74 @@ __global__ void __launch_bounds__(64) setup_tables_kernel(
             }
             b0 = -kv - C;
         }
-        if (r >= 0) b0_out[(size_t)k * N + r] = b0;
         lam_t[(size_t)k * nmax + j] = static_cast<Real>(lv);
         drift0[(size_t)k * nmax + j] = static_cast<Real>(-kv * dt);
         frozen[(size_t)k * nmax + j] = static_cast<Real>(b0 * dt);
     }
 }
 
+// E at the 64 nodes and the frozen drift on them, [K][N][Q] and [K][N] FP64:
+// what lll_plan_tables shows and the training labels integrate on (made only
+// for plans that hold the table).  One block of 64 threads (node q) per step.
+__global__ void __launch_bounds__(64) full_tables_kernel(
+    const double *__restrict__ delta, const double *__restrict__ L0,
+    const double *__restrict__ vol, const double *__restrict__ x_in,
+    const double *__restrict__ w_in, const double *__restrict__ kappa, int N, int s, int driver,
+    double c, double *__restrict__ E_out, double *__restrict__ b0_out) {
+    __shared__ double cq[LLL_N_MAX_MP][kQ];    // W E_q R_q contributions per rate
+    const int k = blockIdx.x;
+    const int q = threadIdx.x;
+    const int m = k / s;
+    const double *lam = vol + (size_t)k * N;
+    const double xq = x_in[q], wq = w_in[q];
+    const bool nig = (driver == kNig);
+    double R = 0.0;
+    for (int r = N - 1; r >= 0; --r) {
+        double E = 0.0;
+        if (r >= m && nig) {
+            E = expm1(lam[r] * xq);
+            cq[r][q] = wq * E * R;
+            const double ell0 = delta[r] * L0[r] / (1.0 + delta[r] * L0[r]);
+            R = R + ell0 * E * (1.0 + R);
+        }
+        E_out[((size_t)k * N + r) * kQ + q] = E;
+    }
+    __syncthreads();
+    if (q < N) {
+        double b0 = 0.0;
+        if (q >= m) {
+            double C = 0.0, S = 0.0;
+            if (nig) {
+                for (int i = 0; i < kQ; ++i) C += cq[q][i];
+            } else {
+                for (int l = q + 1; l < N; ++l)
+                    S += delta[l] * L0[l] / (1.0 + delta[l] * L0[l]) * lam[l];
+                C = c * lam[q] * S;
+            }
+            b0 = -kappa[(size_t)k * N + q] - C;
+        }
+        b0_out[(size_t)k * N + q] = b0;
+    }
+}
+
 template <typename Real>
 hipError_t launch_precompute_t(const lll_plan &p, hipStream_t st) {
     const DeviceTables &d = p.d;
-    hipLaunchKernelGGL(setup_rule_kernel<Real>, dim3(1), dim3(64), 0, st, d.tenor, d.delta, d.L0,
-                       d.vol, p.N, p.s, p.off, p.driver, p.alpha, p.beta, p.delta_nig, p.c, d.x,
-                       d.w, d.steps, d.lam_pm, static_cast<Real *>(d.cinv), d.L0s, d.deltas,
-                       p.nmax);
+    hipLaunchKernelGGL(setup_rule_kernel<Real>, dim3(p.N), dim3(kRuleBlock), 0, st, d.tenor,
+                       d.delta, d.L0, d.vol, p.N, p.s, p.off, p.driver, p.alpha, p.beta,
+                       p.delta_nig, p.c, d.x, d.w, d.steps, d.lam_pm, static_cast<Real *>(d.cinv),
+                       d.L0s, d.deltas, p.nmax, d.gx, d.gw, d.nq);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(setup_tables_kernel<Real>, dim3(p.K), dim3(64), 0, st, d.tenor, d.delta,
-                       d.L0, d.vol, d.x, d.w, p.N, p.s, p.off, p.nmax, p.driver, p.alpha, p.beta,
-                       p.delta_nig, p.c, d.kappa, d.E, d.b0, static_cast<Real *>(d.ew),
+    hipLaunchKernelGGL(setup_tables_kernel<Real>, dim3(p.K), dim3(256), 0, st, d.tenor, d.delta,
+                       d.L0, d.vol, d.gx, d.gw, d.nq, p.N, p.s, p.off, p.nmax, p.driver, p.alpha,
+                       p.beta, p.delta_nig, p.c, d.kappa, static_cast<Real *>(d.ew),
                        static_cast<Real *>(d.lam), static_cast<Real *>(d.drift0),
                        static_cast<Real *>(d.frozen), static_cast<Real *>(d.dt));
+    e = hipGetLastError();
+    if (e != hipSuccess || !d.E) return e;
+    hipLaunchKernelGGL(full_tables_kernel, dim3(p.K), dim3(64), 0, st, d.delta, d.L0, d.vol, d.x,
+                       d.w, d.kappa, p.N, p.s, p.driver, p.c, d.E, d.b0);
     return hipGetLastError();
 }
 
