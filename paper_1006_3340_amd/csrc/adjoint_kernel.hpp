@@ -68,7 +68,7 @@ __device__ __forceinline__ float increment_f(const PathArgs<float> &a, int k, in
     const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
     const uint4 w = philox4x32_10(make_uint4(static_cast<uint32_t>(k), p_lo, p_hi, a.stream_word),
                                   a.key0, a.key1);
-    return static_cast<float>(increment(w, cst, a.beta, a.brownian != 0, nullptr));
+    return static_cast<float>(increment(w, cst, a.brownian != 0, nullptr));
 }
 
 template <int NMAX, int J0>

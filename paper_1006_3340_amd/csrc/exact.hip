@@ -423,7 +423,7 @@ exact_period_kernel(PathArgs<Real> a, cptr<Real> kex,
                                static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32),
                                a.stream_word),
                     a.key0, a.key1);
-                inc = static_cast<Real>(increment(w, cst, a.beta, a.brownian != 0, nullptr));
+                inc = static_cast<Real>(increment(w, cst, a.brownian != 0, nullptr));
             }
         }
         Real dH[T];

@@ -255,7 +255,7 @@ mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
         const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
         const uint4 w = philox4x32_10(
             make_uint4(static_cast<uint32_t>(k), p_lo, p_hi, a.stream_word), a.key0, a.key1);
-        const float dH = static_cast<float>(increment(w, cst, a.beta, false, nullptr));
+        const float dH = static_cast<float>(increment(w, cst, false, nullptr));
         const int j0 = a.off + m;
         float C[kSlots];
         uint64_t oob = 0;

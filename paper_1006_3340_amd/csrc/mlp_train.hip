@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(kBlock) record_kernel(PathArgs<float> a, int R
         const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
         const uint4 w = philox4x32_10(
             make_uint4(static_cast<uint32_t>(k), p_lo, p_hi, a.stream_word), a.key0, a.key1);
-        const float dH = static_cast<float>(increment(w, cst, a.beta, false, nullptr));
+        const float dH = static_cast<float>(increment(w, cst, false, nullptr));
         detail::dispatch_step<float, NMAX, kFull>(std::make_integer_sequence<int, NMAX>{}, j0, a,
                                                   k, dH, X, X1);
     }

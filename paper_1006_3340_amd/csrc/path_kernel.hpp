@@ -65,7 +65,7 @@ struct PathArgs {
     int64_t n_paths, path_offset;
     int N, s, S, off, brownian, product;
     uint32_t stream_word, key0, key1;
-    double beta, c;
+    double c;
 };
 
 __device__ __forceinline__ float ell_of(float x, float cinv) {
@@ -472,7 +472,7 @@ __device__ __forceinline__ void simulate_lds(const PathArgs<Real> &a, int64_t gi
         const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
         const uint4 w = philox4x32_10(
             make_uint4(static_cast<uint32_t>(k), p_lo, p_hi, a.stream_word), a.key0, a.key1);
-        const Real dH = static_cast<Real>(increment(w, cst, a.beta, brownian, nullptr));
+        const Real dH = static_cast<Real>(increment(w, cst, brownian, nullptr));
         const int j0 = a.off + m;
         dispatch_step_lds<Real, NMAX, SCHEME>(std::make_integer_sequence<int, NMAX>{}, j0, a, k, dH,
                                               xs, pred);
@@ -523,7 +523,7 @@ __device__ __forceinline__ void simulate(const PathArgs<Real> &a, int64_t gid) {
         const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
         const uint4 w = philox4x32_10(
             make_uint4(static_cast<uint32_t>(k), p_lo, p_hi, a.stream_word), a.key0, a.key1);
-        const Real dH = static_cast<Real>(increment(w, cst, a.beta, brownian, nullptr));
+        const Real dH = static_cast<Real>(increment(w, cst, brownian, nullptr));
         const int j0 = a.off + m;
         dispatch_step<Real, NMAX, SCHEME>(std::make_integer_sequence<int, NMAX>{}, j0, a, k, dH, X,
                                           pred);
@@ -618,7 +618,6 @@ inline PathArgs<Real> make_args(const lll_plan &p, uint64_t seed, int64_t n_path
     a.stream_word = p.struct_id & 0xFFFFFFu;
     a.key0 = static_cast<uint32_t>(seed & 0xFFFFFFFFull);
     a.key1 = static_cast<uint32_t>(seed >> 32);
-    a.beta = p.beta;
     a.c = p.c;
     return a;
 }

@@ -34,8 +34,7 @@ namespace {
 __global__ void __launch_bounds__(kBlock) increments_kernel(const double *__restrict__ steps, int k,
                                                             int s, int64_t p0, int64_t n,
                                                             uint32_t stream_word, uint32_t key0,
-                                                            uint32_t key1, double beta,
-                                                            int brownian, double *__restrict__ V,
+                                                            uint32_t key1, int brownian, double *__restrict__ V,
                                                             double *__restrict__ dH) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (i >= n) return;
@@ -47,7 +46,7 @@ __global__ void __launch_bounds__(kBlock) increments_kernel(const double *__rest
                    static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32), stream_word),
         key0, key1);
     double v;
-    dH[i] = increment(w, cst, beta, brownian != 0, &v);
+    dH[i] = increment(w, cst, brownian != 0, &v);
     V[i] = v;
 }
 
@@ -216,7 +215,7 @@ hipError_t launch_increments(const lll_plan &p, int k, int64_t p0, int64_t n, ui
     const dim3 grid(static_cast<unsigned>((n + kBlock - 1) / kBlock));
     hipLaunchKernelGGL(increments_kernel, grid, dim3(kBlock), 0, st, p.d.steps, k, p.s, p0, n,
                        p.struct_id & 0xFFFFFFu, static_cast<uint32_t>(seed & 0xFFFFFFFFull),
-                       static_cast<uint32_t>(seed >> 32), p.beta,
+                       static_cast<uint32_t>(seed >> 32),
                        p.driver == LLL_DRIVER_BROWNIAN ? 1 : 0, V_dev, dH_dev);
     return hipGetLastError();
 }

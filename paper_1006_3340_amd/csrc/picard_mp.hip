@@ -58,7 +58,6 @@ struct MpArgs {
     int64_t path_base;                      // global index of the chunk's first path
     int G, N, s, K, off, nmax;
     uint32_t stream_word, key0, key1;
-    double beta;
 };
 
 // ell^ is stored for the live rates only: step k of period m holds rates
@@ -112,7 +111,7 @@ __global__ void __launch_bounds__(kBlock) mp_increments_kernel(MpArgs a) {
     const uint4 w = philox4x32_10(make_uint4(static_cast<uint32_t>(k), static_cast<uint32_t>(path),
                                              static_cast<uint32_t>(path >> 32), a.stream_word),
                                   a.key0, a.key1);
-    a.dh[e] = static_cast<float>(increment(w, cst, a.beta, false, nullptr));
+    a.dh[e] = static_cast<float>(increment(w, cst, false, nullptr));
 }
 
 // Table values and driver increments of steps kb .. kb+3 (clamped to the last
@@ -536,7 +535,6 @@ hipError_t launch_picard_mp(const lll_plan &p, int64_t n_paths, int64_t path_off
     a.stream_word = pa.stream_word;
     a.key0 = pa.key0;
     a.key1 = pa.key1;
-    a.beta = p.beta;
     for (int64_t first = 0; first < n_paths; first += p.mp_chunk) {
         const int64_t n_chunk = n_paths - first < p.mp_chunk ? n_paths - first : p.mp_chunk;
         a.path_base = path_offset + first;

@@ -203,13 +203,14 @@ __global__ void __launch_bounds__(kRuleBlock) setup_rule_kernel(
             double *sc = steps + 4 * t;
             if (driver == kNig) {
                 const double gamma = sqrt(alpha * alpha - beta * beta);
-                sc[0] = delta_nig * dt / gamma;                 // IG mean
-                sc[1] = (delta_nig * dt) * (delta_nig * dt);    // IG shape
-                sc[2] = -delta_nig * beta / gamma * dt;         // mu_H dt
-                sc[3] = 0.0;
+                const double mean = delta_nig * dt / gamma;
+                sc[0] = 0.5 * sqrt(mean) / (delta_nig * dt);  // IG shape (delta dt)^2
+                sc[1] = beta * mean;
+                sc[2] = sqrt(mean);
+                sc[3] = -delta_nig * beta / gamma * dt;       // mu_H dt
             } else {
-                sc[0] = sc[1] = sc[2] = 0.0;
-                sc[3] = sqrt(c * dt);
+                sc[0] = sc[1] = sc[3] = 0.0;
+                sc[2] = sqrt(c * dt);
             }
         }
         if (t < nmax) {
