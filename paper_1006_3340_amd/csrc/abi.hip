@@ -234,14 +234,14 @@ int create_plan(const lll_term_structure *ts, int precision, int64_t max_paths, 
     A(&d.chunks, (size_t)p->max_chunks * N * nstat);
     A(&d.sums, N * nstat);
     A(&d.results, 3 * N * S + 2 * N);
-    d.gw = d.gx + N * lll::kQSize;
-    d.nq = reinterpret_cast<int *>(d.gw + N * lll::kQSize);
     if (e != hipSuccess) {
         free_tables(d);
         delete p;
         return fail(e == hipErrorOutOfMemory ? LLL_ENOMEM : LLL_EHIP, "device allocation: %s",
                     hipGetErrorString(e));
     }
+    d.gw = d.gx + N * lll::kQSize;
+    d.nq = reinterpret_cast<int *>(d.gw + N * lll::kQSize);
     auto H2D = [&](double *dst, const std::vector<double> &src) {
         if (e == hipSuccess) e = hipMemcpy(dst, src.data(), src.size() * sizeof(double),
                                            hipMemcpyHostToDevice);
