@@ -8,15 +8,12 @@
 namespace lll {
 namespace adj {
 
-extern template hipError_t launch_adjoint_bucket<8>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
-extern template hipError_t launch_adjoint_bucket<16>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
-extern template hipError_t launch_adjoint_bucket<20>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
-extern template hipError_t launch_adjoint_bucket<24>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
-extern template hipError_t launch_adjoint_bucket<32>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
-extern template hipError_t launch_adjoint_bucket<40>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
 #define LLL_VJP_EXTERN(NM)                                                                         \
     extern template hipError_t launch_vjp_bucket<NM>(const PathArgs<float> &, const AdjArgs &,    \
-                                                     const VjpArgs &, hipStream_t);
+                                                     const VjpArgs &, hipStream_t);          \
+    extern template hipError_t launch_adjoint_bucket<NM>(const PathArgs<float> &,             \
+                                                         const AdjArgs &, const SideStreams &, \
+                                                         hipStream_t);
 LLL_VJP_EXTERN(8)
 LLL_VJP_EXTERN(16)
 LLL_VJP_EXTERN(20)
@@ -27,14 +24,14 @@ LLL_VJP_EXTERN(40)
 
 namespace {
 
-// Tables of the reverse sweep: x_q e^{lambda x_q} = dE/dlambda per (step, node,
-// slot), kappa'(lambda) dt per (step, slot), the weights in FP32 and 1/L(0,T).
+// Tables of the reverse sweep: E per (step, node, slot), kappa'(lambda) dt per
+// (step, slot), the nodes and weights in FP32 and 1/L(0,T).
 // NIG: kappa'(u) = mu_H + delta (beta + u) / sqrt(alpha^2 - (beta + u)^2).
 __global__ void __launch_bounds__(64) setup_adjoint_tables_kernel(
     const double *__restrict__ tenor, const double *__restrict__ L0, const double *__restrict__ vol,
     const double *__restrict__ gx, const double *__restrict__ gw, const int *__restrict__ nq, int N,
-    int s, int off, int nmax, double alpha, double beta, double delta_nig, float *__restrict__ xe,
-    float *__restrict__ dkap, float *__restrict__ w32, double *__restrict__ inv_L0) {
+    int s, int off, int nmax, double alpha, double beta, double delta_nig, float *__restrict__ E,
+    float *__restrict__ dkap, float *__restrict__ xw, double *__restrict__ inv_L0) {
     const int k = blockIdx.x;
     const int q = threadIdx.x;
     const int m = k / s;
@@ -44,8 +41,8 @@ __global__ void __launch_bounds__(64) setup_adjoint_tables_kernel(
     for (int j = 0; j < nmax && q < nq[k]; ++j) {
         const int r = j - off;
         double v = 0.0;
-        if (r >= m) v = xq * exp(vol[(size_t)k * N + r] * xq);
-        xe[((size_t)k * kQ + q) * nmax + j] = static_cast<float>(v);
+        if (r >= m) v = expm1(vol[(size_t)k * N + r] * xq);
+        E[((size_t)k * kQ + q) * nmax + j] = static_cast<float>(v);
     }
     if (q < nmax) {
         const int r = q - off;
@@ -58,7 +55,10 @@ __global__ void __launch_bounds__(64) setup_adjoint_tables_kernel(
         }
         dkap[(size_t)k * nmax + q] = static_cast<float>(d);
     }
-    if (k == m * s && q < nq[k]) w32[m * kQ + q] = static_cast<float>(gw[m * kQ + q]);
+    if (k == m * s && q < nq[k]) {
+        xw[2 * (m * kQ + q)] = static_cast<float>(xq);
+        xw[2 * (m * kQ + q) + 1] = static_cast<float>(gw[m * kQ + q]);
+    }
     if (k == 0) {
         if (q < nmax) inv_L0[q] = (q - off >= 0) ? 1.0 / L0[q - off] : 0.0;
     }
@@ -150,47 +150,80 @@ __global__ void __launch_bounds__(256) reduce_cols_kernel(const double *__restri
 }  // namespace
 }  // namespace adj
 
+namespace {
+
+// The states of the forward pass, the increments, the fixings and the carried
+// adjoint take 4 (s N (N+1) / 2 + K + 2 N) bytes per path (34 KB at 40 rates and 10
+// steps per period): paths go in chunks that keep them within this many bytes
+// (524,000 paths there, 8 wavefronts per SIMD).
+constexpr int64_t kStateBytes = int64_t(16) << 30;
+
+int64_t state_rows(const lll_plan &p) {  // see AdjArgs
+    return int64_t(p.s) * (p.N * (p.N + 1) / 2) + p.K + 2 * p.N;
+}
+
+}  // namespace
+
 hipError_t greeks_alloc(lll_plan &p) {
-    if (p.g.ckpt) return hipSuccess;
-    const size_t N = p.N, K = p.K, NM = p.nmax, P = p.max_paths, S = p.s;
     GreeksBuffers &g = p.g;
+    if (g.chunk) return hipSuccess;
+    const size_t N = p.N, K = p.K, NM = p.nmax;
     hipError_t e = hipSuccess;
     auto A = [&](void **ptr, size_t bytes) {
         if (e == hipSuccess) e = hipMalloc(ptr, bytes + 64);
     };
-    A((void **)&g.xe, K * kQSize * NM * sizeof(float));
+    A((void **)&g.E, K * kQSize * NM * sizeof(float));
     A((void **)&g.dkap, K * NM * sizeof(float));
-    A((void **)&g.w32, N * kQSize * sizeof(float));
+    A((void **)&g.xw, N * kQSize * 2 * sizeof(float));
     A((void **)&g.inv_L0, NM * sizeof(double));
-    A((void **)&g.ckpt, N * (N + 1) / 2 * P * sizeof(float));
-    A((void **)&g.fix, N * P * sizeof(float));
-    A((void **)&g.scr, S * NM * P * sizeof(float));
-    A((void **)&g.scr_dh, S * P * sizeof(float));
     A((void **)&g.gpart, (size_t)p.max_waves * N * 2 * N * sizeof(double));
     A((void **)&g.gchunks, (size_t)p.max_chunks * N * 2 * N * sizeof(double));
     A((void **)&g.gsums, N * 2 * N * sizeof(double));
     A((void **)&g.out, (2 * N * N + N) * sizeof(double));
-    A((void **)&g.vjp_xb, N * P * sizeof(float));
     A((void **)&g.vjp_out, 3 * N * sizeof(double));
     A((void **)&g.vjp_g, N * sizeof(double));
     A((void **)&g.vjp_w, N * sizeof(float));
-    return e;
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&g.ss.fork, hipEventDisableTiming);
+    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i) {
+        e = hipStreamCreateWithFlags(&g.ss.side[i], hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&g.ss.join[i], hipEventDisableTiming);
+    }
+    if (e != hipSuccess) return e;
+    const int64_t all = (p.max_paths + kBlock - 1) / kBlock * kBlock;
+    int64_t chunk = kStateBytes / (4 * state_rows(p)) / kBlock * kBlock;
+    if (chunk < kBlock) chunk = kBlock;
+    if (chunk > all) chunk = all;
+    for (;; chunk = (chunk / 2 + kBlock - 1) / kBlock * kBlock) {  // less where memory is short
+        e = hipMalloc((void **)&g.rows, (size_t)chunk * 4 * state_rows(p));
+        if (e != hipErrorOutOfMemory || chunk <= 64 * kBlock) break;
+        (void)hipGetLastError();
+    }
+    if (e != hipSuccess) {
+        g.rows = nullptr;
+        return e;
+    }
+    g.chunk = chunk;
+    return hipSuccess;
 }
 
 void greeks_free(lll_plan &p) {
     GreeksBuffers &g = p.g;
-    void *ptrs[] = {g.xe, g.dkap, g.w32, g.inv_L0, g.ckpt, g.fix, g.scr, g.scr_dh, g.gpart,
-                    g.gchunks, g.gsums, g.out, g.vjp_xb, g.vjp_out, g.vjp_g, g.vjp_w};
+    void *ptrs[] = {g.E, g.dkap, g.xw, g.inv_L0, g.rows, g.gpart, g.gchunks, g.gsums, g.out,
+                    g.vjp_out, g.vjp_g, g.vjp_w};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
+    for (int i = 0; i < kSideStreams; ++i) {
+        if (g.ss.side[i]) (void)hipStreamDestroy(g.ss.side[i]);
+        if (g.ss.join[i]) (void)hipEventDestroy(g.ss.join[i]);
+    }
+    if (g.ss.fork) (void)hipEventDestroy(g.ss.fork);
     p.g = GreeksBuffers{};
 }
 
 namespace {
 
 // Precompute, the adjoint tables and the kernel arguments of a Greeks pass.
-hipError_t adjoint_setup(const lll_plan &p, int64_t n_paths, uint64_t seed, hipStream_t st,
-                         adj::AdjArgs &g) {
+hipError_t adjoint_setup(const lll_plan &p, hipStream_t st, adj::AdjArgs &g) {
     using namespace adj;
     const DeviceTables &d = p.d;
     const GreeksBuffers &gb = p.g;
@@ -198,19 +231,28 @@ hipError_t adjoint_setup(const lll_plan &p, int64_t n_paths, uint64_t seed, hipS
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(setup_adjoint_tables_kernel, dim3(p.K), dim3(64), 0, st, d.tenor, d.L0,
                        d.vol, d.gx, d.gw, d.nq, p.N, p.s, p.off, p.nmax, p.alpha, p.beta,
-                       p.delta_nig, gb.xe, gb.dkap, gb.w32, gb.inv_L0);
+                       p.delta_nig, gb.E, gb.dkap, gb.xw, gb.inv_L0);
     e = hipGetLastError();
-    g.xe = detail::as_const<float>(gb.xe);
+    g.E = detail::as_const<float>(gb.E);
     g.dkap = detail::as_const<float>(gb.dkap);
-    g.w = detail::as_const<float>(gb.w32);
+    g.xw = detail::as_const<float>(gb.xw);
     g.inv_L0 = detail::as_const<double>(gb.inv_L0);
-    g.ckpt = gb.ckpt;
-    g.fix = gb.fix;
-    g.scr = gb.scr;
-    g.scr_dh = gb.scr_dh;
-    g.gpart = gb.gpart;
-    g.n_paths = n_paths;
+    g.rows = gb.rows;
+    g.n_rows = state_rows(p);
     return e;
+}
+
+// The kernels' arguments for the paths [first, first + chunk) of the pass: its
+// waves' partials, and the states of one chunk.  Chunks are whole blocks, so the
+// wave sums do not depend on the chunking.
+bool next_chunk(const lll_plan &p, int64_t n_paths, uint64_t seed, int64_t first, int cols,
+                detail::PathArgs<float> &a, adj::AdjArgs &g) {
+    if (first >= n_paths) return false;
+    const int64_t n = n_paths - first < p.g.chunk ? n_paths - first : p.g.chunk;
+    a = detail::make_args<float>(p, seed, n, first, nullptr);
+    a.partials += first / kWave * p.N * (3 * p.S + 2);
+    g.gpart = p.g.gpart + first / kWave * cols;
+    return true;
 }
 
 // Fixed-order column sums of rows x cols per-wave partials into `out` (via the
@@ -234,9 +276,9 @@ hipError_t launch_greeks_vjp(const lll_plan &p, int64_t n_paths, uint64_t seed,
     using namespace adj;
     const GreeksBuffers &gb = p.g;
     AdjArgs g;
-    hipError_t e = adjoint_setup(p, n_paths, seed, st, g);
+    hipError_t e = adjoint_setup(p, st, g);
     if (e != hipSuccess) return e;
-    PathArgs<float> a = detail::make_args<float>(p, seed, n_paths, 0, nullptr);
+    PathArgs<float> a;
     const int64_t waves = (n_paths + kWave - 1) / kWave;
     const int64_t n_part = waves * 2 * p.N;
     hipLaunchKernelGGL(zero_kernel, dim3(static_cast<unsigned>((n_part + 255) / 256)), dim3(256), 0,
@@ -251,17 +293,19 @@ hipError_t launch_greeks_vjp(const lll_plan &p, int64_t n_paths, uint64_t seed,
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     VjpArgs v;
-    v.xb = gb.vjp_xb;
-    v.part = gb.gpart;
     v.w = detail::as_const<float>(gb.vjp_w);
-    switch (p.nmax) {
-        case 8: e = launch_vjp_bucket<8>(a, g, v, st); break;
-        case 16: e = launch_vjp_bucket<16>(a, g, v, st); break;
-        case 20: e = launch_vjp_bucket<20>(a, g, v, st); break;
-        case 24: e = launch_vjp_bucket<24>(a, g, v, st); break;
-        case 32: e = launch_vjp_bucket<32>(a, g, v, st); break;
-        case 40: e = launch_vjp_bucket<40>(a, g, v, st); break;
-        default: return hipErrorInvalidValue;
+    for (int64_t first = 0;
+         e == hipSuccess && next_chunk(p, n_paths, seed, first, 2 * p.N, a, g); first += gb.chunk) {
+        v.part = g.gpart;
+        switch (p.nmax) {
+            case 8: e = launch_vjp_bucket<8>(a, g, v, st); break;
+            case 16: e = launch_vjp_bucket<16>(a, g, v, st); break;
+            case 20: e = launch_vjp_bucket<20>(a, g, v, st); break;
+            case 24: e = launch_vjp_bucket<24>(a, g, v, st); break;
+            case 32: e = launch_vjp_bucket<32>(a, g, v, st); break;
+            case 40: e = launch_vjp_bucket<40>(a, g, v, st); break;
+            default: return hipErrorInvalidValue;
+        }
     }
     if (e != hipSuccess) return e;
     e = launch_reduce(p, n_paths, st);  // prices
@@ -279,18 +323,21 @@ hipError_t launch_greeks(const lll_plan &p, int64_t n_paths, uint64_t seed, hipS
     const DeviceTables &d = p.d;
     const GreeksBuffers &gb = p.g;
     AdjArgs g;
-    hipError_t e = adjoint_setup(p, n_paths, seed, st, g);
+    hipError_t e = adjoint_setup(p, st, g);
     if (e != hipSuccess) return e;
-    PathArgs<float> a = detail::make_args<float>(p, seed, n_paths, 0, nullptr);
-    switch (p.nmax) {
-        case 8: e = launch_adjoint_bucket<8>(a, g, st); break;
-        case 16: e = launch_adjoint_bucket<16>(a, g, st); break;
-        case 20: e = launch_adjoint_bucket<20>(a, g, st); break;
-        case 24: e = launch_adjoint_bucket<24>(a, g, st); break;
-        case 32: e = launch_adjoint_bucket<32>(a, g, st); break;
-        case 40: e = launch_adjoint_bucket<40>(a, g, st); break;
-        default: return hipErrorInvalidValue;
-    }
+    PathArgs<float> a;
+    for (int64_t first = 0;
+         e == hipSuccess && next_chunk(p, n_paths, seed, first, 2 * p.N * p.N, a, g);
+         first += gb.chunk)
+        switch (p.nmax) {
+            case 8: e = launch_adjoint_bucket<8>(a, g, gb.ss, st); break;
+            case 16: e = launch_adjoint_bucket<16>(a, g, gb.ss, st); break;
+            case 20: e = launch_adjoint_bucket<20>(a, g, gb.ss, st); break;
+            case 24: e = launch_adjoint_bucket<24>(a, g, gb.ss, st); break;
+            case 32: e = launch_adjoint_bucket<32>(a, g, gb.ss, st); break;
+            case 40: e = launch_adjoint_bucket<40>(a, g, gb.ss, st); break;
+            default: return hipErrorInvalidValue;
+        }
     if (e != hipSuccess) return e;
     e = launch_reduce(p, n_paths, st);  // prices
     if (e != hipSuccess) return e;

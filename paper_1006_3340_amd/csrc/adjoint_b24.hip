@@ -4,7 +4,8 @@
 
 namespace lll {
 namespace adj {
-template hipError_t launch_adjoint_bucket<24>(const PathArgs<float> &, const AdjArgs &, hipStream_t);
+template hipError_t launch_adjoint_bucket<24>(const PathArgs<float> &, const AdjArgs &,
+                                               const SideStreams &, hipStream_t);
 template hipError_t launch_vjp_bucket<24>(const PathArgs<float> &, const AdjArgs &, const VjpArgs &,
                                            hipStream_t);
 }  // namespace adj

@@ -11,21 +11,28 @@
 // ell_l = delta_l L_l / (1 + delta_l L_l), L_l = L(0, T_l) e^{X_l}.
 //
 // Rate i depends only on rates l >= i, so the sweep of caplet i carries only
-// those.  Memory: the forward pass checkpoints the live rates at every tenor
-// date (packed, N (N+1) / 2 floats per path) and the fixing of every rate;
-// each sweep recomputes one period at a time from its checkpoint into a
-// per-period scratch (steps_per_period states per path) and walks it back.
+// those.  Memory: the forward pass keeps the live rates at the start of every step
+// (packed, s N (N+1) / 2 floats per path), the increments and the fixing of every
+// rate, and the sweeps read them back, a step ahead of their use; paths go in
+// chunks that hold the states within kStateBytes.  Recomputing each period from
+// a checkpoint at its tenor date instead (an increment, a FULL step and the same
+// traffic through a scratch, per step) and three table entries per rate and node
+// took price and gradient of 40 rates from 12.1 to 15.5 ms at 2^18 paths, the
+// Jacobian from 33 to 66 ms at 2^17.  What bounds it now is the vector ALU at the
+// two wavefronts per SIMD that 6 registers per rate leave the wide sweeps.
 //
 // Reverse of one step, per node q (the suffix products P by a downward pass,
 // then an upward pass with F_l = sum_{i<l} Cbar_i W E_{i,q} prod_{i<m<l} beta_m):
 //     ellbar_l += E_{l,q} P_l F_l
 //     Ebar_l    = Cbar_l W_q (P_l - 1) + ell_l P_l F_l,  lambdabar_l += x_q e^{lambda_l x_q} Ebar_l
 //     F_{l+1}   = (1 + ell_l E_{l,q}) F_l + Cbar_l W_q E_{l,q},     Cbar_l = -dt Xbar_l,
+// with W_q moved from F into P, so that E is the only table entry per rate and
+// node: a node's row then fits the scalar registers in one batch of loads
+// (gradient kernels 10.2 -> 8.1 ms at 2^18 paths),
 // then Xbar_l += ellbar_l ell_l (1 - ell_l), L0bar_l += ellbar_l ell_l (1 - ell_l) / L(0, T_l),
-// lambdabar_l += Xbar_l (dH - kappa'(lambda_l) dt).  The per-lane L0 accumulators
-// sum the unscaled increments ellbar_l ell_l (1 - ell_l); the factor 1 / L(0, T_l),
-// the same for every step, multiplies their wavefront sum (no per-step constant
-// held in registers).
+// lambdabar_l += Xbar_l (dH - kappa'(lambda_l) dt).  L0bar_l L(0, T_l) collects the
+// same terms as Xbar_l, from the payoff's adjoint down to step 0, so it is Xbar_l
+// at the start: its wavefront sum is scaled by 1 / L(0, T_l) once.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -45,21 +52,38 @@ using detail::PathArgs;
 constexpr int kAdjBlock = 64;  // one wavefront per block: per-lane accumulators in LDS
 
 struct AdjArgs {
-    cptr<float> xe;        // [K][Q][nmax]  x_q e^{lambda x_q}
+    cptr<float> E;         // [K][Q][nmax]  e^{lambda x_q} - 1
     cptr<float> dkap;      // [K][nmax]     kappa'(lambda) dt
-    cptr<float> w;         // [N][Q]        quadrature weights of each period
+    cptr<float> xw;        // [N][Q][2]     nodes and weights of each period
     cptr<double> inv_L0;   // [nmax]        1 / L(0, T)
-    float *ckpt;           // [N (N+1) / 2][n_paths] live rates at the start of each period
-    float *fix;            // [N][n_paths]  X_i at its fixing
-    float *scr;            // [s][nmax][n_paths] states within one period
-    float *scr_dh;         // [s][n_paths]
+    // per wavefront, rows of 64 lanes (a rate's row is a constant distance from the
+    // next one's, so a step's loads share one address): s N (N+1) / 2 rows of states
+    // (live rates at the start of each step), K of increments, N of fixings, N of
+    // the state adjoint carried between the periods of a vector-Jacobian product
+    float *rows;
+    int64_t n_rows;        // rows per wavefront
     double *gpart;         // [waves][N][2N] per-wave sums of L0bar (first N) and vbar
-    int64_t n_paths;
 };
 
-// Packed checkpoint row of rate r at the start of period m (r >= m).
-__device__ __forceinline__ int64_t ckpt_row(int N, int m, int r) {
-    return static_cast<int64_t>(m) * N - (static_cast<int64_t>(m) * (m - 1)) / 2 + (r - m);
+// This lane's column of its wavefront's rows.
+__device__ __forceinline__ float *lane_rows(const AdjArgs &g, int64_t gid) {
+    return g.rows + (gid / kWave) * g.n_rows * kWave + gid % kWave;
+}
+
+// Offsets in a lane's column: rate r at the start of step js of period m (r >= m),
+// the increment of step k, the fixing of rate r, its carried adjoint.
+__device__ __forceinline__ int64_t at_state(const PathArgs<float> &a, int m, int js, int r) {
+    return kWave * (static_cast<int64_t>(a.s) * (m * a.N - (m * (m - 1)) / 2) + js * (a.N - m) +
+                    (r - m));
+}
+__device__ __forceinline__ int64_t at_dh(const PathArgs<float> &a, int k) {
+    return kWave * (static_cast<int64_t>(a.s) * (a.N * (a.N + 1) / 2) + k);
+}
+__device__ __forceinline__ int64_t at_fix(const PathArgs<float> &a, int r) {
+    return at_dh(a, a.N * a.s) + kWave * r;
+}
+__device__ __forceinline__ int64_t at_xb(const PathArgs<float> &a, int r) {
+    return at_fix(a, a.N) + kWave * r;
 }
 
 __device__ __forceinline__ float increment_f(const PathArgs<float> &a, int k, int m, uint32_t p_lo,
@@ -72,22 +96,21 @@ __device__ __forceinline__ float increment_f(const PathArgs<float> &a, int k, in
 }
 
 template <int NMAX, int J0>
-__device__ __forceinline__ void store_ckpt(const PathArgs<float> &a, const AdjArgs &g, int m,
-                                           int64_t gid, bool active, const float (&X)[NMAX]) {
-    if (!active) return;
+__device__ __forceinline__ void store_state(const PathArgs<float> &a, int m, int js, float *d,
+                                            const float (&X)[NMAX]) {
+    float *row = d + at_state(a, m, js, J0 - a.off);
 #pragma unroll
-    for (int j = J0; j < NMAX; ++j)
-        g.ckpt[ckpt_row(a.N, m, j - a.off) * g.n_paths + gid] = X[j];
+    for (int j = J0; j < NMAX; ++j) row[(j - J0) * kWave] = X[j];
 }
 
 template <int NMAX, int... Js>
-__device__ __forceinline__ void dispatch_ckpt(std::integer_sequence<int, Js...>, int j0,
-                                              const PathArgs<float> &a, const AdjArgs &g, int m,
-                                              int64_t gid, bool active, const float (&X)[NMAX]) {
-    (void)((j0 == Js ? (store_ckpt<NMAX, Js>(a, g, m, gid, active, X), 0) : 0) + ...);
+__device__ __forceinline__ void dispatch_store(std::integer_sequence<int, Js...>, int j0,
+                                               const PathArgs<float> &a, int m, int js, float *d,
+                                               const float (&X)[NMAX]) {
+    (void)((j0 == Js ? (store_state<NMAX, Js>(a, m, js, d, X), 0) : 0) + ...);
 }
 
-// Forward FULL pass with checkpoints; also the price partials of PRODUCT
+// Forward FULL pass that keeps its states; also the price partials of PRODUCT
 // (LLL_CAPLETS or LLL_SWAPTIONS, fixed at compile time: the product's payoff
 // code is inlined at every fixing date).
 template <int NMAX, int PRODUCT>
@@ -96,6 +119,7 @@ __device__ void forward(const PathArgs<float> &a, const AdjArgs &g, int64_t gid,
     const uint32_t p_lo = static_cast<uint32_t>(p);
     const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32);
     float X[NMAX], X1[NMAX];
+    float *d = lane_rows(g, gid);
 #pragma unroll
     for (int j = 0; j < NMAX; ++j) {
         X[j] = 0.0f;
@@ -103,20 +127,19 @@ __device__ void forward(const PathArgs<float> &a, const AdjArgs &g, int64_t gid,
     }
     for (int m = 0; m < a.N; ++m) {
         const int j0 = a.off + m;
-        dispatch_ckpt<NMAX>(std::make_integer_sequence<int, NMAX>{}, j0, a, g, m, gid, active, X);
         for (int js = 0; js < a.s; ++js) {
             const int k = m * a.s + js;
             const float dH = increment_f(a, k, m, p_lo, p_hi);
+            dispatch_store<NMAX>(std::make_integer_sequence<int, NMAX>{}, j0, a, m, js, d, X);
+            d[at_dh(a, k)] = dH;
             detail::dispatch_step<float, NMAX, kFull>(std::make_integer_sequence<int, NMAX>{}, j0,
                                                       a, k, dH, X, X1);
         }
-        if (active) {
-            // X of the rate that fixes now (slot j0), selected from registers
-            float xf = 0.0f;
+        // X of the rate that fixes now (slot j0), selected from registers
+        float xf = 0.0f;
 #pragma unroll
-            for (int j = 0; j < NMAX; ++j) xf = (j == j0) ? X[j] : xf;
-            g.fix[static_cast<int64_t>(m) * g.n_paths + gid] = xf;
-        }
+        for (int j = 0; j < NMAX; ++j) xf = (j == j0) ? X[j] : xf;
+        d[at_fix(a, m)] = xf;
         detail::dispatch_payoff<float, NMAX, PRODUCT>(std::make_integer_sequence<int, NMAX>{}, j0,
                                                       a, m, gid, active, X);
     }
@@ -133,6 +156,7 @@ __device__ void forward_lds(const PathArgs<float> &a, const AdjArgs &g, int64_t 
     const uint32_t p_lo = static_cast<uint32_t>(p);
     const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32);
     float X1[NMAX];
+    float *d = lane_rows(g, gid);
 #pragma unroll
     for (int j = 0; j < NMAX; ++j) {
         xs[j * kBlock] = 0.0f;
@@ -140,91 +164,118 @@ __device__ void forward_lds(const PathArgs<float> &a, const AdjArgs &g, int64_t 
     }
     for (int m = 0; m < a.N; ++m) {
         const int j0 = a.off + m;
-        if (active)
-            for (int j = j0; j < NMAX; ++j)
-                g.ckpt[ckpt_row(a.N, m, j - a.off) * g.n_paths + gid] = xs[j * kBlock];
         for (int js = 0; js < a.s; ++js) {
             const int k = m * a.s + js;
             const float dH = increment_f(a, k, m, p_lo, p_hi);
+            float *row = d + at_state(a, m, js, m);
+            for (int j = j0; j < NMAX; ++j, row += kWave) *row = xs[j * kBlock];
+            d[at_dh(a, k)] = dH;
             detail::dispatch_step_lds<float, NMAX, kFull>(std::make_integer_sequence<int, NMAX>{}, j0,
                                                           a, k, dH, xs, X1);
         }
-        if (active) g.fix[static_cast<int64_t>(m) * g.n_paths + gid] = xs[j0 * kBlock];
+        d[at_fix(a, m)] = xs[j0 * kBlock];
         detail::payoff_lds<float, NMAX, PRODUCT>(a, m, gid, active, xs, j0);
     }
 }
 
-// Reverse of Euler step k for the slots JC .. NMAX-1, given the state X at the
-// start of the step and Xb = adjoint of the state at its end (updated in place
-// to the adjoint at the start).  Parameter adjoints go to the LDS accumulators.
+// X of the slots JC .. NMAX-1 at the start of step js of period m.
+template <int NMAX, int JC>
+__device__ __forceinline__ void load_state(const PathArgs<float> &a, int m, int js, const float *d,
+                                           float (&X)[NMAX]) {
+    const float *row = d + at_state(a, m, js, JC - a.off);
+#pragma unroll
+    for (int j = JC; j < NMAX; ++j) X[j] = row[(j - JC) * kWave];
+}
+
+// X at the start of the step before step js of period m.
+template <int NMAX, int JC>
+__device__ __forceinline__ void load_before(const PathArgs<float> &a, int m, int js,
+                                            const float *d, float (&X)[NMAX]) {
+    if (js > 0) load_state<NMAX, JC>(a, m, js - 1, d, X);
+    else load_state<NMAX, JC>(a, m - 1, a.s - 1, d, X);
+}
+
+// A reverse step holds X (loaded ahead), ell, Xb, P, lb, vb, a temporary and the vol
+// accumulators per rate: 8 registers, two wavefronts per SIMD up to 30 rates.
+// Beyond, the accumulators stay in LDS; beyond 34 rates, X is loaded after the node
+// loop instead of ahead of it.
+template <int NMAX, int JC>
+constexpr bool kAccInLds = NMAX - JC > 30;
+template <int NMAX, int JC>
+constexpr bool kLoadAhead = NMAX - JC <= 34;
+
+// Reverse of step js of period m for the slots JC .. NMAX-1, given the state X
+// at the start of the step and Xb = adjoint of the state at its end (updated in
+// place to the adjoint at the start); X is then loaded with the state of the step
+// before.  The vol adjoints go to the LDS accumulators.
 template <int NMAX, int JC>
 __device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const AdjArgs &g, int m,
-                                             int k, float dH, const float (&X)[NMAX], float (&Xb)[NMAX],
-                                             float *__restrict__ accL0, float *__restrict__ accV) {
-    // Cbar = -dt Xbar: the factor -dt is applied once after the node loop
-    // (lb and vb below are the adjoints divided by -dt).
-    const int lane = threadIdx.x;
+                                             int js, const float *d, float (&X)[NMAX],
+                                             float (&Xb)[NMAX], float *__restrict__ accV) {
+    // Cbar = -dt Xbar: the factor -dt is applied to lb after the node loop and to
+    // the node x in the vol adjoints
+    const int k = m * a.s + js;
+    const float dH = d[at_dh(a, k)];
     const float mdt = -a.dt[k];
     const cptr<float> dk = g.dkap + (size_t)k * NMAX;
+    if constexpr (kAccInLds<NMAX, JC>) __asm__ volatile("" ::: "memory");
     float ell[NMAX], lb[NMAX], vb[NMAX], P[NMAX];
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) {
         ell[j] = detail::ell_of(X[j], a.cinv[j]);
         lb[j] = 0.0f;
-        vb[j] = Xb[j] * (dH - dk[j]) / mdt;
+        vb[j] = 0.0f;
     }
-    cptr<float> row = a.ew + (size_t)k * kQ * NMAX * 2;
-    cptr<float> xrow = g.xe + (size_t)k * kQ * NMAX;
+    if (kLoadAhead<NMAX, JC> && k > 0) load_before<NMAX, JC>(a, m, js, d, X);
+    cptr<float> row = g.E + (size_t)k * kQ * NMAX;
     const int nq = a.nq[k];
 #pragma unroll 1
-    for (int q = 0; q < nq; ++q, row += NMAX * 2, xrow += NMAX) {
-        const float W = g.w[m * kQ + q];
-        P[NMAX - 1] = 1.0f;
+    for (int q = 0; q < nq; ++q, row += NMAX) {
+        const float x = g.xw[2 * (m * kQ + q)] * mdt, W = g.xw[2 * (m * kQ + q) + 1];
+        P[NMAX - 1] = W;  // W times the suffix products
 #pragma unroll
-        for (int j = NMAX - 2; j >= JC; --j)
-            P[j] = P[j + 1] * fmaf(ell[j + 1], row[2 * (j + 1)], 1.0f);
-        float F = 0.0f;
+        for (int j = NMAX - 2; j >= JC; --j) P[j] = P[j + 1] * fmaf(ell[j + 1], row[j + 1], 1.0f);
+        float F = 0.0f;  // F of the header / W
 #pragma unroll
         for (int j = JC; j < NMAX; ++j) {
-            const float E = row[2 * j];
-            const float WE = row[2 * j + 1];
+            const float E = row[j];
             const float G = P[j] * F;
             lb[j] = fmaf(E, G, lb[j]);
-            const float WR = fmaf(P[j], W, -W);  // W (P - 1)
-            const float Eb = fmaf(Xb[j], WR, ell[j] * G);
-            vb[j] = fmaf(xrow[j], Eb, vb[j]);
-            F = fmaf(fmaf(ell[j], E, 1.0f), F, Xb[j] * WE);
+            const float xEb = x * fmaf(Xb[j], P[j] - W, ell[j] * G);
+            vb[j] = fmaf(E, xEb, vb[j] + xEb);  // x e^{lambda x} Ebar = x (1 + E) Ebar
+            F = fmaf(E, fmaf(ell[j], F, Xb[j]), F);
         }
     }
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) {
-        const float t = lb[j] * mdt * ell[j] * (1.0f - ell[j]);
-        Xb[j] += t;
-        accL0[(j - JC) * kAdjBlock + lane] += t;
-        accV[(j - JC) * kAdjBlock + lane] += vb[j] * mdt;
+        accV[(j - JC) * kAdjBlock] += fmaf(Xb[j], dH - dk[j], vb[j]);
+        Xb[j] += lb[j] * mdt * ell[j] * (1.0f - ell[j]);
+    }
+    if (!kLoadAhead<NMAX, JC> && k > 0) {
+        __asm__ volatile("" ::: "memory");
+        load_before<NMAX, JC>(a, m, js, d, X);
     }
 }
 
 // Adds w times the payoff adjoint of product c (strike 0; slot JC = off + c)
-// at its fixing date T_{c+1} to the state adjoint Xb and the L0 accumulators,
-// and loads the fixing state into X.
+// at its fixing date T_{c+1} to the state adjoint Xb, and loads the fixing state
+// into X.
 //   caplet:   f = D (L_c - K)^+, D = prod_{l>c}(1 + delta_l L_l);
 //   swaption: f = (Q - 1 - K A)^+, Q = prod_{l>=c} b_l, b_l = 1 + delta_l L_l,
 //             A = sum_{l>=c} delta_l prod_{j>l} b_j, so that with
 //             S_l = sum_{c<=m<l} delta_m prod_{j>m} b_j = sum_{c<=m<l} delta_m Q / prod_{c<=j<=m} b_j
 //             df/dX_l = ell_l (Q - K S_l) where the payoff is positive.
-// The direct L0 terms are df/dX_l / L(0, T_l) (L = L(0,T) e^X at fixed X); the
-// accumulators hold the df/dX_l terms, scaled by 1 / L(0, T_l) after the wave sum.
+// The direct L0 terms are df/dX_l / L(0, T_l) (L = L(0,T) e^X at fixed X).  The
+// scheduling barriers keep the FP64 quantities of one rate at a time in registers:
+// interleaved over the rates they set the register count of the whole sweep (330
+// at 40 rates, one wavefront per SIMD).
 template <int NMAX, int JC>
-__device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const AdjArgs &g, int64_t gl,
+__device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const float *d,
                                             bool active, float w, float (&X)[NMAX],
-                                            float (&Xb)[NMAX], float *__restrict__ accL0) {
-    const int lane = threadIdx.x;
+                                            float (&Xb)[NMAX]) {
     const int c = JC - a.off;
-    X[JC] = g.fix[static_cast<int64_t>(c) * g.n_paths + gl];
-#pragma unroll
-    for (int j = JC + 1; j < NMAX; ++j)
-        X[j] = g.ckpt[ckpt_row(a.N, c + 1, j - a.off) * g.n_paths + gl];
+    X[JC] = d[at_fix(a, c)];
+    if constexpr (JC + 1 < NMAX) load_state<NMAX, JC + 1>(a, c + 1, 0, d, X);
     if (a.product == LLL_SWAPTIONS) {
         double Q = 1.0, A = 0.0;
 #pragma unroll
@@ -232,6 +283,7 @@ __device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const AdjA
             const double b = 1.0 + a.deltas[j] * (a.L0s[j] * static_cast<double>(expf(X[j])));
             A = fma(a.deltas[j], Q, A);
             Q *= b;
+            __builtin_amdgcn_sched_barrier(0);
         }
         const double K = a.strikes[c * a.S];
         const bool itm = active && ((Q - 1.0) - K * A > 0.0);
@@ -240,11 +292,10 @@ __device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const AdjA
         for (int j = JC; j < NMAX; ++j) {
             const double L = a.L0s[j] * static_cast<double>(expf(X[j]));
             const double b = 1.0 + a.deltas[j] * L;
-            const float t = itm ? w * static_cast<float>(a.deltas[j] * L / b * (Q - K * S)) : 0.0f;
-            Xb[j] += t;
-            accL0[(j - JC) * kAdjBlock + lane] += t;
+            Xb[j] += itm ? w * static_cast<float>(a.deltas[j] * L / b * (Q - K * S)) : 0.0f;
             pre *= b;
             S = fma(a.deltas[j], Q / pre, S);
+            __builtin_amdgcn_sched_barrier(0);
         }
         return;
     }
@@ -255,6 +306,7 @@ __device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const AdjA
         const double L = a.L0s[j] * static_cast<double>(expf(X[j]));
         D *= 1.0 + a.deltas[j] * L;
         ellf[j] = static_cast<float>(a.deltas[j] * L / (1.0 + a.deltas[j] * L));
+        __builtin_amdgcn_sched_barrier(0);
     }
     const double Lc = a.L0s[JC] * static_cast<double>(expf(X[JC]));
     const double K = a.strikes[c * a.S];
@@ -263,86 +315,40 @@ __device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const AdjA
     const float dD = itm ? w * static_cast<float>(Lc - K) : 0.0f;
     const float Df = static_cast<float>(D);
     Xb[JC] += dXc;
-    accL0[lane] += dXc;
 #pragma unroll
-    for (int j = JC + 1; j < NMAX; ++j) {
-        const float t = dD * Df * ellf[j];
-        Xb[j] += t;
-        accL0[(j - JC) * kAdjBlock + lane] += t;
-    }
-}
-
-// Reverse of period m for the slots JC .. NMAX-1: recompute the period from
-// its checkpoint, keeping every step's state in the scratch, then walk the
-// steps back, updating Xb from the adjoint at the period's end to the one at
-// its start.
-template <int NMAX, int JC>
-__device__ __forceinline__ void reverse_period(const PathArgs<float> &a, const AdjArgs &g, int m,
-                                               int64_t gl, bool active, uint32_t p_lo,
-                                               uint32_t p_hi, float (&X)[NMAX], float (&X1)[NMAX],
-                                               float (&Xb)[NMAX], float *__restrict__ accL0,
-                                               float *__restrict__ accV) {
-#pragma unroll
-    for (int j = JC; j < NMAX; ++j) X[j] = g.ckpt[ckpt_row(a.N, m, j - a.off) * g.n_paths + gl];
-    for (int js = 0; js < a.s; ++js) {
-        const int k = m * a.s + js;
-        const float dH = increment_f(a, k, m, p_lo, p_hi);
-        if (active) {
-#pragma unroll
-            for (int j = JC; j < NMAX; ++j)
-                g.scr[(static_cast<int64_t>(js) * NMAX + j) * g.n_paths + gl] = X[j];
-            g.scr_dh[static_cast<int64_t>(js) * g.n_paths + gl] = dH;
-        }
-        detail::step<float, NMAX, kFull, JC>(a, k, dH, X, X1);
-    }
-    for (int js = a.s - 1; js >= 0; --js) {
-        const int k = m * a.s + js;
-#pragma unroll
-        for (int j = JC; j < NMAX; ++j)
-            X[j] = g.scr[(static_cast<int64_t>(js) * NMAX + j) * g.n_paths + gl];
-        const float dH = g.scr_dh[static_cast<int64_t>(js) * g.n_paths + gl];
-        reverse_step<NMAX, JC>(a, g, m, k, dH, X, Xb, accL0, accV);
-    }
+    for (int j = JC + 1; j < NMAX; ++j) Xb[j] += dD * Df * ellf[j];
 }
 
 // Sweep of the caplet fixing in slot JC (rate c = JC - off, period c).
 template <int NMAX, int JC>
-__device__ __forceinline__ void sweep(const PathArgs<float> &a, const AdjArgs &g, int64_t gid, bool active,
-                      float *__restrict__ accL0, float *__restrict__ accV) {
+__device__ __forceinline__ void sweep(const PathArgs<float> &a, const AdjArgs &g, int64_t gid,
+                                      bool active, float *__restrict__ accV) {
     const int lane = threadIdx.x;
     const int c = JC - a.off;
     const int N = a.N;
-    const int64_t p = a.path_offset + gid;
-    const uint32_t p_lo = static_cast<uint32_t>(p);
-    const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32);
-    const int64_t gl = active ? gid : 0;  // lanes past the end read path 0 and contribute 0
+    const float *d = lane_rows(g, gid);
 #pragma unroll
-    for (int j = JC; j < NMAX; ++j) {
-        accL0[(j - JC) * kAdjBlock + lane] = 0.0f;
-        accV[(j - JC) * kAdjBlock + lane] = 0.0f;
-    }
-    float X[NMAX], X1[NMAX], Xb[NMAX];
+    for (int j = JC; j < NMAX; ++j) accV[(j - JC) * kAdjBlock + lane] = 0.0f;
+    float X[NMAX], Xb[NMAX];
 #pragma unroll
-    for (int j = 0; j < NMAX; ++j) {
-        X[j] = 0.0f;
-        X1[j] = 0.0f;
-        Xb[j] = 0.0f;
-    }
-    seed_caplet<NMAX, JC>(a, g, gl, active, 1.0f, X, Xb, accL0);
+    for (int j = 0; j < NMAX; ++j) Xb[j] = 0.0f;
+    seed_caplet<NMAX, JC>(a, d, active, 1.0f, X, Xb);
     // skip the sweep when no lane of the wavefront has a nonzero adjoint
     bool any = false;
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) any = any || (Xb[j] != 0.0f);
     if (__any(any)) {
+        load_state<NMAX, JC>(a, c, a.s - 1, d, X);
         for (int m = c; m >= 0; --m)
-            reverse_period<NMAX, JC>(a, g, m, gl, active, p_lo, p_hi, X, X1, Xb, accL0, accV);
+            for (int js = a.s - 1; js >= 0; --js)
+                reverse_step<NMAX, JC>(a, g, m, js, d, X, Xb, accV + lane);
     }
-    // wavefront sums of this caplet's adjoints
+    // wavefront sums of this caplet's adjoints (lanes past the end: Xb = 0)
     const int64_t wave = gid / kWave;
     double *out = g.gpart + (static_cast<int64_t>(wave) * N + c) * 2 * N;
+#pragma unroll
     for (int j = JC; j < NMAX; ++j) {
-        const double l0 =
-            detail::wave_sum(active ? accL0[(j - JC) * kAdjBlock + lane] : 0.0f) * g.inv_L0[j];
+        const double l0 = detail::wave_sum(Xb[j]) * g.inv_L0[j];
         const double vv = detail::wave_sum(active ? accV[(j - JC) * kAdjBlock + lane] : 0.0f);
         if (lane == 0) {
             out[j - a.off] = l0;
@@ -361,10 +367,10 @@ __device__ __forceinline__ void sweep(const PathArgs<float> &a, const AdjArgs &g
 // it takes the state adjoint carried from period m+1 (xb, by rate), adds the
 // seed of caplet m (weight w_m = g_m delta_m) at its fixing, reverses the
 // period and stores the adjoint at the period's start; the wavefront sums of
-// its parameter adjoints are added to the per-wave partials (periods in
-// launch order, so the sums are deterministic).
+// its vol adjoints are added to the per-wave partials (periods in launch order,
+// so the sums are deterministic), and the kernel of period 0 writes those of the
+// adjoint at the start.
 struct VjpArgs {
-    float *xb;      // [N][n_paths] state adjoint by rate, carried between periods
     double *part;   // [waves][2N] sums of L0bar (first N) and vbar
     detail::cptr<float> w;  // [N] seeds g_m s_m of the products (device memory)
 };
@@ -372,48 +378,44 @@ struct VjpArgs {
 template <int NMAX, int JC>
 __device__ __forceinline__ void vjp_period(const PathArgs<float> &a, const AdjArgs &g,
                                            const VjpArgs &v, int64_t gid, bool active,
-                                           float *__restrict__ accL0, float *__restrict__ accV) {
+                                           float *__restrict__ accV) {
     const int lane = threadIdx.x;
     const int m = JC - a.off;
     const float w = v.w[m];
     const int N = a.N;
-    const int64_t p = a.path_offset + gid;
-    const uint32_t p_lo = static_cast<uint32_t>(p);
-    const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32);
-    const int64_t gl = active ? gid : 0;
+    float *d = lane_rows(g, gid);
+    float *xb = d + at_xb(a, m);
 #pragma unroll
-    for (int j = JC; j < NMAX; ++j) {
-        accL0[(j - JC) * kAdjBlock + lane] = 0.0f;
-        accV[(j - JC) * kAdjBlock + lane] = 0.0f;
-    }
-    float X[NMAX], X1[NMAX], Xb[NMAX];
-#pragma unroll
-    for (int j = 0; j < NMAX; ++j) {
-        X[j] = 0.0f;
-        X1[j] = 0.0f;
-        Xb[j] = 0.0f;
-    }
+    for (int j = JC; j < NMAX; ++j) accV[(j - JC) * kAdjBlock + lane] = 0.0f;
+    float X[NMAX], Xb[NMAX];
+    Xb[JC] = 0.0f;
     // rate m is fixed after period m: only the later rates carry an adjoint
 #pragma unroll
     for (int j = JC + 1; j < NMAX; ++j)
-        Xb[j] = active ? v.xb[static_cast<int64_t>(j - a.off) * g.n_paths + gid] : 0.0f;
-    seed_caplet<NMAX, JC>(a, g, gl, active, w, X, Xb, accL0);
+        Xb[j] = m < N - 1 ? xb[(j - JC) * kWave] : 0.0f;
+    seed_caplet<NMAX, JC>(a, d, active, w, X, Xb);
     bool any = false;
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) any = any || (Xb[j] != 0.0f);
-    if (__any(any)) reverse_period<NMAX, JC>(a, g, m, gl, active, p_lo, p_hi, X, X1, Xb, accL0, accV);
-    if (active) {
+    if (__any(any)) {
+        load_state<NMAX, JC>(a, m, a.s - 1, d, X);
+        for (int js = a.s - 1; js >= 0; --js) reverse_step<NMAX, JC>(a, g, m, js, d, X, Xb, accV + lane);
+    }
+    if (m > 0) {
 #pragma unroll
-        for (int j = JC; j < NMAX; ++j) v.xb[static_cast<int64_t>(j - a.off) * g.n_paths + gid] = Xb[j];
+        for (int j = JC; j < NMAX; ++j) xb[(j - JC) * kWave] = Xb[j];
     }
     double *out = v.part + (gid / kWave) * 2 * N;
+#pragma unroll
     for (int j = JC; j < NMAX; ++j) {
-        const double l0 =
-            detail::wave_sum(active ? accL0[(j - JC) * kAdjBlock + lane] : 0.0f) * g.inv_L0[j];
         const double vv = detail::wave_sum(active ? accV[(j - JC) * kAdjBlock + lane] : 0.0f);
-        if (lane == 0) {
-            out[j - a.off] += l0;
-            out[N + j - a.off] += vv;
+        if (lane == 0) out[N + j - a.off] += vv;
+    }
+    if (m == 0) {
+#pragma unroll
+        for (int j = JC; j < NMAX; ++j) {
+            const double l0 = detail::wave_sum(Xb[j]) * g.inv_L0[j];
+            if (lane == 0) out[j - a.off] = l0;
         }
     }
 }
@@ -421,26 +423,24 @@ __device__ __forceinline__ void vjp_period(const PathArgs<float> &a, const AdjAr
 // One launch per caplet (slot JC): each sweep is its own kernel so that its
 // register allocation covers only its own live set.
 template <int NMAX, int JC>
-__global__ void __launch_bounds__(kAdjBlock) sweep_kernel(PathArgs<float> a, AdjArgs g) {
+__global__ void __launch_bounds__(kAdjBlock, (kAccInLds<NMAX, JC> ? 2 : 1)) sweep_kernel(PathArgs<float> a, AdjArgs g) {
     // per-lane accumulators of the carried slots JC..NMAX-1 only (LDS bounds
     // the resident wavefronts of the long sweeps)
-    __shared__ float accL0[(NMAX - JC) * kAdjBlock];
     __shared__ float accV[(NMAX - JC) * kAdjBlock];
     const int64_t gid = static_cast<int64_t>(blockIdx.x) * kAdjBlock + threadIdx.x;
     const int64_t wave_first = gid - threadIdx.x;
     if (wave_first >= a.n_paths) return;
-    sweep<NMAX, JC>(a, g, gid, gid < a.n_paths, accL0, accV);
+    sweep<NMAX, JC>(a, g, gid, gid < a.n_paths, accV);
 }
 
 template <int NMAX, int JC>
-__global__ void __launch_bounds__(kAdjBlock) vjp_period_kernel(PathArgs<float> a, AdjArgs g,
-                                                               VjpArgs v) {
-    __shared__ float accL0[(NMAX - JC) * kAdjBlock];
+__global__ void __launch_bounds__(kAdjBlock, (kAccInLds<NMAX, JC> ? 2 : 1))
+    vjp_period_kernel(PathArgs<float> a, AdjArgs g, VjpArgs v) {
     __shared__ float accV[(NMAX - JC) * kAdjBlock];
     const int64_t gid = static_cast<int64_t>(blockIdx.x) * kAdjBlock + threadIdx.x;
     const int64_t wave_first = gid - threadIdx.x;
     if (wave_first >= a.n_paths) return;
-    vjp_period<NMAX, JC>(a, g, v, gid, gid < a.n_paths, accL0, accV);
+    vjp_period<NMAX, JC>(a, g, v, gid, gid < a.n_paths, accV);
 }
 
 template <int NMAX, int PRODUCT>
@@ -508,7 +508,7 @@ hipError_t launch_forward(dim3 grid, const PathArgs<float> &a, const AdjArgs &g,
     return hipGetLastError();
 }
 
-// Forward pass with checkpoints, then the periods from the last to the first
+// Forward pass, then the periods from the last to the first
 // (v.w[m] = weight of product m times its price scale; v.part must be zero).
 template <int NMAX>
 hipError_t launch_vjp_bucket(const PathArgs<float> &a, const AdjArgs &g, const VjpArgs &v,
@@ -520,13 +520,27 @@ hipError_t launch_vjp_bucket(const PathArgs<float> &a, const AdjArgs &g, const V
     return e;
 }
 
-// Forward pass with checkpoints, then one sweep launch per caplet.
+// Forward pass, then one sweep launch per caplet.  The sweeps are independent and
+// write their own rows of the partials: they go round the caller's stream and the
+// side streams, so that the many of them that leave the SIMDs short of wavefronts
+// (2^17 paths: two per SIMD and launch) run beside each other.
 template <int NMAX>
-hipError_t launch_adjoint_bucket(const PathArgs<float> &a, const AdjArgs &g, hipStream_t st) {
+hipError_t launch_adjoint_bucket(const PathArgs<float> &a, const AdjArgs &g, const SideStreams &ss,
+                                 hipStream_t st) {
     const dim3 grid(static_cast<unsigned>((a.n_paths + kAdjBlock - 1) / kAdjBlock));
     hipError_t e = launch_forward<NMAX>(grid, a, g, st);
-    for (int c = 0; c < a.N && e == hipSuccess; ++c)
-        e = launch_sweep<NMAX>(std::make_integer_sequence<int, NMAX>{}, a.off + c, grid, a, g, st);
+    if (e == hipSuccess) e = hipEventRecord(ss.fork, st);
+    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i)
+        e = hipStreamWaitEvent(ss.side[i], ss.fork, 0);
+    for (int c = 0; c < a.N && e == hipSuccess; ++c) {
+        const int i = c % (kSideStreams + 1);
+        e = launch_sweep<NMAX>(std::make_integer_sequence<int, NMAX>{}, a.off + c, grid, a, g,
+                               i == 0 ? st : ss.side[i - 1]);
+    }
+    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i) {
+        e = hipEventRecord(ss.join[i], ss.side[i]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, ss.join[i], 0);
+    }
     return e;
 }
 

@@ -67,12 +67,18 @@ struct MlpBuffers {
     double *stats = nullptr;
     int64_t stat_waves = 0;
 };
+constexpr int kSideStreams = 3;  // with the caller's stream, the device's four queues
+struct SideStreams {             // launches beside the caller's stream (default priority)
+    hipStream_t side[kSideStreams] = {};
+    hipEvent_t fork = nullptr, join[kSideStreams] = {};
+};
 struct GreeksBuffers {
-    float *xe = nullptr, *dkap = nullptr, *w32 = nullptr;
+    SideStreams ss;
+    float *E = nullptr, *dkap = nullptr, *xw = nullptr;
     double *inv_L0 = nullptr;
-    float *ckpt = nullptr, *fix = nullptr, *scr = nullptr, *scr_dh = nullptr;
+    float *rows = nullptr;     // the wavefronts' states of one chunk of paths (AdjArgs)
+    int64_t chunk = 0;         // paths of a chunk
     double *gpart = nullptr, *gchunks = nullptr, *gsums = nullptr, *out = nullptr;
-    float *vjp_xb = nullptr;   // [N][paths] state adjoint carried between periods
     double *vjp_g = nullptr;   // [N] the weights g of the vector-Jacobian product
     float *vjp_w = nullptr;    // [N] g_i times the product's price scale (delta_i or 1)
     double *vjp_out = nullptr; // [3N] price, sum_i g_i dP_i/dL0, sum_i g_i dP_i/dvol
