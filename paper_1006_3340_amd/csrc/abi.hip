@@ -725,9 +725,8 @@ int lll_batch_create(const lll_term_structure *ts, int n_ts, int64_t max_paths_e
         }
         b->plans.push_back(p);
     }
-    b->max_items = static_cast<int>(items);
     hipError_t e = hipMalloc(&b->args, n_ts * lll::batch_args_bytes());
-    if (e == hipSuccess) e = hipMalloc(&b->items, (size_t)b->max_items * lll::batch_item_bytes());
+    if (e == hipSuccess) e = hipMalloc(&b->items, (size_t)n_ts * lll::batch_item_bytes());
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&b->counter), 64 * sizeof(int) * lll::kBatchBuckets);
     if (e != hipSuccess) {
@@ -796,20 +795,12 @@ int lll_batch_execute(lll_batch *batch, int scheme, int64_t n_paths_each, uint64
                     (long long)batch->max_paths_each);
     hipStream_t st = as_stream(stream);
     hipError_t e = hipSuccess;
-    for (lll_plan *p : batch->plans) {
-        e = lll::launch_precompute(*p, st);
-        if (e != hipSuccess) return hip_fail(e, "precompute launch");
-    }
     e = lll::batch_prepare(*batch, n_paths_each, seed, st);
-    if (e != hipSuccess) return hip_fail(e, "preparing batch items");
+    if (e != hipSuccess) return hip_fail(e, "preparing the batch");
     if (batch->timing) e = hipEventRecord(batch->ev[0], st);
     if (e == hipSuccess) e = lll::launch_batched(*batch, scheme, st);
     if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
-    if (batch->timing) e = hipEventRecord(batch->ev[1], st);
-    if (e != hipSuccess) return hip_fail(e, "recording timing event");
     for (lll_plan *p : batch->plans) {
-        e = lll::launch_reduce(*p, n_paths_each, st);
-        if (e != hipSuccess) return hip_fail(e, "reduction launch");
         p->last_n_paths = n_paths_each;
         p->executed = true;
     }

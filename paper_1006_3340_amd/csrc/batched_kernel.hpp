@@ -1,7 +1,7 @@
 // batched_kernel.hpp -- the persistent kernel of one register bucket.
 //
 // Work items are (structure, block of 256 paths) of the structures whose rates
-// fit the bucket NMAX; a grid sized to the kernel's resident capacity pulls
+// fit the bucket NMAX, structure by structure; a grid sized to the kernel's resident capacity pulls
 // items from a device counter until none are left.  Each structure keeps its
 // own precompute tables (laid out for its bucket) behind a per-structure
 // argument block.  Instantiated per bucket in batched_b*.hip.
@@ -21,10 +21,12 @@ namespace batch {
 using detail::cptr;
 using detail::PathArgs;
 
-struct BatchItem {
-    int32_t s;      // structure
-    int32_t pad;
-    int64_t first;  // first path of the block
+// The structures of a bucket in the order of their items, and what a pass sets.
+struct BatchWork {
+    cptr<int> order;
+    int n_items, blocks_each;
+    int64_t n_paths;
+    uint32_t key0, key1;
 };
 
 // Copy of a trivially copyable struct read word by word through the constant
@@ -42,7 +44,7 @@ __device__ __forceinline__ T load_uniform(cptr<T> p) {
 
 template <int NMAX, int SCHEME>
 __global__ void __launch_bounds__(kBlock) batched_kernel(cptr<PathArgs<float>> args,
-                                                         cptr<BatchItem> items, int n_items,
+                                                         BatchWork work,
                                                          int *__restrict__ counter) {
     // The block shares one item (its four wavefronts then stream the same
     // step tables through the CU's scalar cache).  With the state in LDS the
@@ -61,23 +63,23 @@ __global__ void __launch_bounds__(kBlock) batched_kernel(cptr<PathArgs<float>> a
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(*slot);
         __syncthreads();
-        if (item >= n_items) return;  // same value in every lane of the block
-        const BatchItem it = load_uniform<BatchItem>(items + item);
-        const PathArgs<float> a = load_uniform<PathArgs<float>>(args + it.s);
-        const int64_t gid = it.first + threadIdx.x;
+        if (item >= work.n_items) return;  // same value in every lane of the block
+        const int at = item / work.blocks_each;
+        PathArgs<float> a = load_uniform<PathArgs<float>>(args + work.order[at]);
+        a.n_paths = work.n_paths;
+        a.key0 = work.key0;
+        a.key1 = work.key1;
+        const int64_t gid =
+            static_cast<int64_t>(item - at * work.blocks_each) * kBlock + threadIdx.x;
         const int64_t wave_first = gid - (threadIdx.x % kWave);
         if (wave_first < a.n_paths)
             detail::simulate<float, NMAX, SCHEME, true, detail::kAnyProduct>(a, gid);
     }
 }
 
-namespace {
-__global__ void zero_counter_kernel(int *counter) { *counter = 0; }
-}  // namespace
-
 template <int NMAX, int SCHEME>
-hipError_t launch_bucket_t(cptr<PathArgs<float>> args, cptr<BatchItem> items, int n_items,
-                           int *counter, hipStream_t st) {
+hipError_t launch_bucket_t(cptr<PathArgs<float>> args, const BatchWork &work, int *counter,
+                           hipStream_t st) {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -85,29 +87,25 @@ hipError_t launch_bucket_t(cptr<PathArgs<float>> args, cptr<BatchItem> items, in
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_kernel<NMAX, SCHEME>,
                                                          kBlock, 0);
     if (e != hipSuccess) return e;
-    const int grid = std::max(1, std::min(cus * std::max(per_cu, 1), n_items));
-    hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const int grid = std::max(1, std::min(cus * std::max(per_cu, 1), work.n_items));
     hipLaunchKernelGGL((batched_kernel<NMAX, SCHEME>), dim3(grid), dim3(kBlock), 0, st, args,
-                       items, n_items, counter);
+                       work, counter);
     return hipGetLastError();
 }
 
-// The persistent launch of one bucket: items[0 .. n_items) all belong to
-// structures of this bucket.
+// The persistent launch of one bucket (the counter starts at zero).
 template <int NMAX>
-hipError_t launch_bucket(int scheme, cptr<PathArgs<float>> args, cptr<BatchItem> items,
-                         int n_items, int *counter, hipStream_t st) {
+hipError_t launch_bucket(int scheme, cptr<PathArgs<float>> args, const BatchWork &work,
+                         int *counter, hipStream_t st) {
     switch (scheme) {
-        case kFull: return launch_bucket_t<NMAX, kFull>(args, items, n_items, counter, st);
-        case kPicard: return launch_bucket_t<NMAX, kPicard>(args, items, n_items, counter, st);
-        default: return launch_bucket_t<NMAX, kFrozen>(args, items, n_items, counter, st);
+        case kFull: return launch_bucket_t<NMAX, kFull>(args, work, counter, st);
+        case kPicard: return launch_bucket_t<NMAX, kPicard>(args, work, counter, st);
+        default: return launch_bucket_t<NMAX, kFrozen>(args, work, counter, st);
     }
 }
 
 #define LLL_BATCH_BUCKET_DECL(EXT, NMAX)                                                          \
-    EXT template hipError_t launch_bucket<NMAX>(int, cptr<PathArgs<float>>, cptr<BatchItem>, int, \
+    EXT template hipError_t launch_bucket<NMAX>(int, cptr<PathArgs<float>>, const BatchWork &,    \
                                                 int *, hipStream_t);
 #ifndef LLL_BATCH_BUCKET_TU
 LLL_BATCH_BUCKET_DECL(extern, 8)

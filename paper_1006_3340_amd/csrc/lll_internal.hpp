@@ -114,10 +114,12 @@ constexpr int kBatchBuckets = 5;  // register buckets of 40, 32, 24, 16 and 8 sl
 struct lll_batch {
     std::vector<lll_plan *> plans;   // one per structure, its own register bucket, FP32
     int64_t max_paths_each = 0, n_paths_each = 0;
-    void *args = nullptr;            // device PathArgs<float>[n]
-    void *items = nullptr;           // device work items, grouped by bucket
+    void *args = nullptr;            // device PathArgs<float>[n], then PassArgs[n]
+    void *items = nullptr;           // device structure order, grouped by bucket
+    bool laid_out = false;           // args and items are on the device
+    int64_t pass_paths = 0;          // paths each and seed of the pass being launched
+    uint64_t pass_seed = 0;
     int *counter = nullptr;          // device work counters, one per bucket (64 ints apart)
-    int n_items = 0, max_items = 0;
     int bucket_begin[lll::kBatchBuckets] = {}, bucket_end[lll::kBatchBuckets] = {};
     hipStream_t side[lll::kBatchBuckets] = {};  // the buckets' launch streams (default priority)
     hipEvent_t fork = nullptr, join[lll::kBatchBuckets] = {};
@@ -157,8 +159,25 @@ size_t batch_args_bytes();
 hipError_t batch_prepare(lll_batch &b, int64_t n_paths_each, uint64_t seed, hipStream_t st);
 hipError_t launch_batched(const lll_batch &b, int scheme, hipStream_t st);
 
+// One structure's buffers and scalars for the set-up and reduction kernels, by
+// value for a plan or one of a device array for a batch (blockIdx.y).
+struct PassArgs {
+    const double *tenor, *delta, *L0, *vol;
+    double *x, *w, *steps, *lam_pm, *L0s, *deltas, *gx, *gw, *kappa;
+    int *nq;
+    void *cinv, *ew, *lam, *drift0, *frozen, *dt;
+    const double *partials;
+    double *chunks, *sums, *results;
+    int N, s, S, off, nmax, driver, product;
+    double alpha, beta, delta_nig, c, B0_T1;
+};
+PassArgs pass_args(const lll_plan &p);  // paths.hip
+
 // precompute.hip
 hipError_t launch_precompute(const lll_plan &p, hipStream_t st);
+// the same for the FP32 structures of a device array, in one launch each kernel
+hipError_t launch_precompute_batch(const PassArgs *many, int structures, int max_N, int max_K,
+                                   hipStream_t st);
 // precompute.hip: replace the initial forwards (L0_dev [N], or NULL) and shift
 // each rate's vol curve from the creation table (shift_dev [N], or NULL)
 hipError_t launch_set_inputs(const lll_plan &p, const double *L0_dev, const double *shift_dev,
@@ -189,6 +208,8 @@ hipError_t launch_exact(const lll_plan &p, int64_t n_paths, int64_t path_offset,
 hipError_t launch_paths(const lll_plan &p, int scheme, int64_t n_paths, int64_t path_offset,
                         uint64_t seed, double *path_fix, hipStream_t st);
 hipError_t launch_reduce(const lll_plan &p, int64_t n_paths, hipStream_t st);
+hipError_t launch_reduce_batch(const PassArgs *many, int structures, int64_t n_paths,
+                               hipStream_t st);
 hipError_t launch_drift(const lll_plan &p, int k, const double *L_dev, int64_t n, double *b_dev,
                         hipStream_t st);
 hipError_t launch_increments(const lll_plan &p, int k, int64_t p0, int64_t n, uint64_t seed,

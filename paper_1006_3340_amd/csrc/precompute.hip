@@ -94,8 +94,10 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 // candidates passes, the period keeps the 64 nodes.
 constexpr int kCand[] = {3, 4, 5, 6, 7, 8, 10, 12, 16, 24};
 constexpr int kNCand = sizeof(kCand) / sizeof(kCand[0]);
+constexpr int kFirstCand = 8;    // the candidates of the first round, one per wavefront
+constexpr int kGaussFirst = 12;  // their largest node count
 constexpr int kGaussMax = 24;
-constexpr int kRuleBlock = 64 * kNCand;
+constexpr int kRuleBlock = 64 * kFirstCand;
 constexpr double kTolF32 = 9.3132257461547852e-10;   // 2^-30
 constexpr double kTolF64 = 7.1054273576010019e-15;   // 2^-47
 
@@ -118,26 +120,35 @@ __device__ __forceinline__ void add_tests(const TestVols &t, double x, double w,
     f[5] = e1 * x;
 }
 
-// One block per accrual period m, one wavefront per candidate node count.  Every
-// block forms the 64-node rule (block 0 also writes it, with Lambda_pm and the
-// per-period and per-slot constants), then its period's Gauss rule.
-// Latency-bound: one launch of N blocks.  The 64 Bessel values are summed by
-// several lanes each and Lambda_pm by 8 lanes a step, and the Gauss-Legendre points
-// are tabulated: with one block of 64 threads iterating for them the rule alone
-// took 85-220 us of every pass.
+// One block per accrual period m (blockIdx.x) and structure (blockIdx.y), one
+// wavefront per candidate node count.  Every block forms the 64-node rule (block 0
+// also writes it, with Lambda_pm and the per-period and per-slot constants), then
+// its period's Gauss rule.  Latency-bound: one launch of N blocks.  The 64 Bessel
+// values are summed by several lanes each and Lambda_pm by 8 lanes a step, the
+// Gauss-Legendre points are tabulated, the nodes found by multisection over the
+// wavefront, and the candidates above 12 nodes run only where none below passes:
+// 30 to 55 us; one wavefront iterating for the 64 nodes alone took 85 to 220 us of
+// every pass.
 template <typename Real>
-__global__ void __launch_bounds__(kRuleBlock) setup_rule_kernel(
-    const double *__restrict__ tenor, const double *__restrict__ delta,
-    const double *__restrict__ L0, const double *__restrict__ vol, int N, int s, int off,
-    int driver, double alpha, double beta, double delta_nig, double c, double *__restrict__ x_out,
-    double *__restrict__ w_out, double *__restrict__ steps, double *__restrict__ lam_pm,
-    Real *__restrict__ cinv, double *__restrict__ L0s, double *__restrict__ deltas, int nmax,
-    double *__restrict__ gx, double *__restrict__ gw, int *__restrict__ nq) {
+__global__ void __launch_bounds__(kRuleBlock) setup_rule_kernel(PassArgs one,
+                                                                const PassArgs *__restrict__ many) {
+    PassArgs pa = one;
+    if (many) pa = many[blockIdx.y];
+    const int N = pa.N, s = pa.s, off = pa.off, driver = pa.driver, nmax = pa.nmax;
+    if (static_cast<int>(blockIdx.x) >= N) return;
+    const double alpha = pa.alpha, beta = pa.beta, delta_nig = pa.delta_nig, c = pa.c;
+    const double *__restrict__ tenor = pa.tenor, *__restrict__ delta = pa.delta;
+    const double *__restrict__ L0 = pa.L0, *__restrict__ vol = pa.vol;
+    double *__restrict__ x_out = pa.x, *__restrict__ w_out = pa.w, *__restrict__ steps = pa.steps;
+    double *__restrict__ lam_pm = pa.lam_pm, *__restrict__ L0s = pa.L0s;
+    double *__restrict__ deltas = pa.deltas, *__restrict__ gx = pa.gx, *__restrict__ gw = pa.gw;
+    Real *__restrict__ cinv = static_cast<Real *>(pa.cinv);
+    int *__restrict__ nq = pa.nq;
     constexpr int kWaves = kRuleBlock / 64;
     __shared__ double red[6][kWaves];
     __shared__ double xs[kQ], ws[kQ];
-    __shared__ double ja[kGaussMax], jb[kGaussMax], mu0s;
-    __shared__ int ok[kWaves];
+    __shared__ double ja[kGaussMax], jb[kGaussMax];
+    __shared__ int ok[kNCand];
     const int t = threadIdx.x, lane = t % 64, wave = t / 64;
     const int K = N * s;
     const int m = blockIdx.x;
@@ -253,12 +264,17 @@ __global__ void __launch_bounds__(kRuleBlock) setup_rule_kernel(
         const double ax = fabs(xq), z = alpha * ax;
         const double h = fmin(0.125, 0.5 / sqrt(z));
         double sum = sub == 0 ? 0.5 : 0.0;  // the u = 0 term counts half
-        for (int i = sub == 0 ? 8 : sub; i < 4000; i += 8) {
-            const double em = expm1(0.5 * i * h);
-            const double sh = 0.5 * (em + em / (1.0 + em));  // sinh(u / 2)
-            const double e = 2.0 * sh * sh;                  // cosh u - 1
+        // em = e^{u/2} - 1 and inv = e^{-u/2} along u = i h, eight points a time
+        const int i0 = sub == 0 ? 8 : sub;
+        double em = expm1(0.5 * i0 * h), inv = 1.0 / (1.0 + em);
+        const double f = expm1(4.0 * h), finv = 1.0 / (1.0 + f);
+        for (int i = i0; i < 4000; i += 8) {
+            const double sh = 0.5 * fma(em, inv, em);  // sinh(u / 2)
+            const double e = 2.0 * sh * sh;            // cosh u - 1
             if (!(z * e <= 50.0)) break;
             sum += exp(-z * e) * (1.0 + e);
+            em = fma(em, f, em) + f;
+            inv *= finv;
         }
         sum = dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(sum)));
         if (sub == 0) {
@@ -280,111 +296,134 @@ __global__ void __launch_bounds__(kRuleBlock) setup_rule_kernel(
     const double Mp = v6[2], Mm = v6[3];
     const double theta = 0.45 * (Mp - Mm);
     const double tilt = exp(theta * xq);
-    if (wave == 0) {
-        const double nu = wq * xq * xq * tilt;
-        const double mu0 = wave_sum_dpp(nu);
-        if (lane == 0) mu0s = mu0;
-        double prev = 0.0, cur = sqrt(nu / mu0), b = 0.0;
-        for (int j = 0; j < kGaussMax; ++j) {
-            const double a = wave_sum_dpp(cur * cur * xq);
-            const double r = (xq - a) * cur - b * prev;
-            const double b2 = wave_sum_dpp(r * r);
-            if (lane == 0) {
-                ja[j] = a;
-                jb[j] = b2;
-            }
-            b = sqrt(b2);
-            prev = cur;
-            cur = b > 0.0 ? r / b : 0.0;
-        }
-    }
-    __syncthreads();
-
-    // This wavefront's candidate: lane i < n finds the i-th node, bisection on the
-    // sign changes of the monic polynomials p_{j+1} = (x - a_j) p_j - b_j^2 p_{j-1}
-    // (their number is the number of nodes above x), then Newton steps
-    const int n = kCand[wave];
-    double lo = -xm, hi = xp;
-    for (int it = 0; it < 26; ++it) {
-        const double x = 0.5 * (lo + hi);
-        double p0 = 1.0, p1 = x - ja[0];
-        int above = p1 < 0.0;
-        for (int j = 1; j < n; ++j) {
-            const double p2 = fma(x - ja[j], p1, -jb[j - 1] * p0);
-            above += (p2 < 0.0) != (p1 < 0.0);
-            p0 = p1;
-            p1 = p2;
-        }
-        if (n - above > lane) hi = x;
-        else lo = x;
-    }
-    double x = 0.5 * (lo + hi);
-    for (int it = 0; it < 4; ++it) {
-        double p0 = 1.0, p1 = x - ja[0], d0 = 0.0, d1 = 1.0;
-        for (int j = 1; j < n; ++j) {
-            const double p2 = fma(x - ja[j], p1, -jb[j - 1] * p0);
-            const double d2 = fma(x - ja[j], d1, fma(-jb[j - 1], d0, p1));
-            p0 = p1;
-            p1 = p2;
-            d0 = d1;
-            d1 = d2;
-        }
-        const double step = p1 / d1;
-        if (fabs(step) <= hi - lo) x -= step;
-    }
-    // weight mu_0 / sum_j p_j(x)^2 / |p_j|^2, then back from the tilted measure;
-    // a node at the origin itself (where x^2 vanishes) moves off it
-    double wt = 0.0;
-    {
-        double p0 = 0.0, p1 = 1.0, nrm = 1.0, sum = 1.0;
-        for (int j = 0; j + 1 < n; ++j) {
-            const double p2 = fma(x - ja[j], p1, -(j ? jb[j - 1] : 0.0) * p0);
-            p0 = p1;
-            p1 = p2;
-            nrm *= jb[j];
-            sum += p1 * p1 / nrm;
-        }
-        if (fabs(x) < 1e-12) x = 1e-12;
-        wt = mu0s / sum / (x * x * exp(theta * x));
-    }
+    const double nu = wq * xq * xq * tilt;
+    const double mu0 = wave_sum_dpp(nu);
+    double prev = 0.0, cur = sqrt(nu / mu0), b = 0.0;  // orthonormal polynomials, wavefront 0
     const TestVols tv{-v6[4], v6[5], Mp, -Mm};
-    double ref[kTests], got[kTests] = {};
+    double ref[kTests];
     add_tests(tv, xq, wq, ref);
-    if (lane < n) add_tests(tv, x, wt, got);
-    bool pass = lane >= n || isfinite(wt);
-    const double tol = sizeof(Real) == 4 ? kTolF32 : kTolF64;
 #pragma unroll
-    for (int i = 0; i < kTests; ++i) {
-        const double fr = wave_sum_dpp(ref[i]), fg = wave_sum_dpp(got[i]);
-        pass = pass && fabs(fg - fr) <= tol * fabs(fr);
-    }
-    pass = __all(pass);
-    if (lane == 0) ok[wave] = pass;
-    __syncthreads();
-    int pick = 0;
-    while (pick < kNCand && !ok[pick]) ++pick;
-    if (pick == wave) {
-        if (lane < n) {
+    for (int i = 0; i < kTests; ++i) ref[i] = wave_sum_dpp(ref[i]);
+    int pick = kNCand;
+    for (int round = 0; round < 2 && pick == kNCand; ++round) {
+        __syncthreads();
+        if (wave == 0)
+            for (int j = round ? kGaussFirst : 0; j < (round ? kGaussMax : kGaussFirst); ++j) {
+                const double a = wave_sum_dpp(cur * cur * xq);
+                const double r = (xq - a) * cur - b * prev;
+                const double b2 = wave_sum_dpp(r * r);
+                if (lane == 0) {
+                    ja[j] = a;
+                    jb[j] = b2;
+                }
+                b = sqrt(b2);
+                prev = cur;
+                cur = b > 0.0 ? r / b : 0.0;
+            }
+        if (t < kNCand) ok[t] = 0;
+        __syncthreads();
+        const int cand = round * kFirstCand + wave;
+        const int n = cand < kNCand ? kCand[cand] : 0;
+        double x = 0.0, wt = 0.0;
+        if (n) {
+            // The nodes: 64 / n lanes a node, multisection on the sign changes of the
+            // monic polynomials p_{j+1} = (x - a_j) p_j - b_j^2 p_{j-1} (their number
+            // is the number of nodes above x), down to 2^-26 of the range
+            const int per = 64 / n, node = min(lane / per, n - 1), part = lane % per;
+            const double width = 1.0 / (per + 1);
+            double lo = -xm, hi = xp;
+            const int its = static_cast<int>(ceil(26.0 / log2(per + 1.0)));
+            for (int it = 0; it < its; ++it) {
+                const double step = (hi - lo) * width;
+                const double at = fma(step, part + 1.0, lo);
+                double p0 = 1.0, p1 = at - ja[0];
+                int above = p1 < 0.0;
+                for (int j = 1; j < n; ++j) {
+                    const double p2 = fma(at - ja[j], p1, -jb[j - 1] * p0);
+                    above += (p2 < 0.0) != (p1 < 0.0);
+                    p0 = p1;
+                    p1 = p2;
+                }
+                // points of this lane's node that lie above it
+                const uint64_t vote = __ballot(lane < n * per && n - above > node);
+                const int below = per - __popcll((vote >> (node * per)) & ((uint64_t(1) << per) - 1));
+                lo = fma(step, static_cast<double>(below), lo);
+                hi = lo + step;
+            }
+            // lane i < n takes node i: Newton steps, then the weight
+            // mu_0 / sum_j p_j(x)^2 / |p_j|^2 back from the tilted measure; a node at
+            // the origin itself (where x^2 vanishes) moves off it
+            const int src = min(lane, n - 1) * per;
+            lo = __shfl(lo, src, 64);
+            hi = __shfl(hi, src, 64);
+            x = 0.5 * (lo + hi);
+            for (int it = 0; it < 3; ++it) {
+                double p0 = 1.0, p1 = x - ja[0], d0 = 0.0, d1 = 1.0;
+                for (int j = 1; j < n; ++j) {
+                    const double p2 = fma(x - ja[j], p1, -jb[j - 1] * p0);
+                    const double d2 = fma(x - ja[j], d1, fma(-jb[j - 1], d0, p1));
+                    p0 = p1;
+                    p1 = p2;
+                    d0 = d1;
+                    d1 = d2;
+                }
+                const double step = p1 / d1;
+                if (fabs(step) <= hi - lo) x -= step;
+            }
+            double p0 = 0.0, p1 = 1.0, nrm = 1.0, sum = 1.0;
+            for (int j = 0; j + 1 < n; ++j) {
+                const double p2 = fma(x - ja[j], p1, -(j ? jb[j - 1] : 0.0) * p0);
+                p0 = p1;
+                p1 = p2;
+                nrm *= jb[j];
+                sum += p1 * p1 / nrm;
+            }
+            if (fabs(x) < 1e-12) x = 1e-12;
+            wt = mu0 / sum / (x * x * exp(theta * x));
+            double got[kTests] = {};
+            if (lane < n) add_tests(tv, x, wt, got);
+            bool pass = lane >= n || isfinite(wt);
+            const double tol = sizeof(Real) == 4 ? kTolF32 : kTolF64;
+#pragma unroll
+            for (int i = 0; i < kTests; ++i)
+                pass = pass && fabs(wave_sum_dpp(got[i]) - ref[i]) <= tol * fabs(ref[i]);
+            pass = __all(pass);
+            if (lane == 0) ok[cand] = pass;
+        }
+        __syncthreads();
+        pick = 0;
+        while (pick < kNCand && !ok[pick]) ++pick;
+        if (pick == cand && lane < n) {
             gx[m * kQ + lane] = x;
             gw[m * kQ + lane] = wt;
         }
-    } else if (pick == kNCand && wave == 0) {
+    }
+    if (pick == kNCand && wave == 0) {
         gx[m * kQ + lane] = xq;
         gw[m * kQ + lane] = wq;
     }
     for (int i = t; i < s; i += kRuleBlock) nq[m * s + i] = pick < kNCand ? kCand[pick] : kQ;
 }
 
-// One block of 256 threads per Euler step k: the cumulants, the tables
+// One block of 256 threads per Euler step k (blockIdx.x) and structure: the cumulants, the tables
 // (E, W E) at the period's nodes, and the frozen drift.
 template <typename Real>
-__global__ void __launch_bounds__(256) setup_tables_kernel(
-    const double *__restrict__ tenor, const double *__restrict__ delta,
-    const double *__restrict__ L0, const double *__restrict__ vol,
-    const double *__restrict__ gx, const double *__restrict__ gw, const int *__restrict__ nq_in,
-    int N, int s, int off, int nmax, int driver, double alpha, double beta, double delta_nig,
-    double c, double *__restrict__ kappa_out, Real *__restrict__ ew, Real *__restrict__ lam_t,
-    Real *__restrict__ drift0, Real *__restrict__ frozen, Real *__restrict__ dt_t) {
+__global__ void __launch_bounds__(256) setup_tables_kernel(PassArgs one,
+                                                           const PassArgs *__restrict__ many) {
+    PassArgs pa = one;
+    if (many) pa = many[blockIdx.y];
+    const int N = pa.N, s = pa.s, off = pa.off, nmax = pa.nmax, driver = pa.driver;
+    if (static_cast<int>(blockIdx.x) >= N * s) return;
+    const double alpha = pa.alpha, beta = pa.beta, delta_nig = pa.delta_nig, c = pa.c;
+    const double *__restrict__ tenor = pa.tenor, *__restrict__ delta = pa.delta;
+    const double *__restrict__ L0 = pa.L0, *__restrict__ vol = pa.vol;
+    const double *__restrict__ gx = pa.gx, *__restrict__ gw = pa.gw;
+    const int *__restrict__ nq_in = pa.nq;
+    double *__restrict__ kappa_out = pa.kappa;
+    Real *__restrict__ ew = static_cast<Real *>(pa.ew), *__restrict__ lam_t = static_cast<Real *>(pa.lam);
+    Real *__restrict__ drift0 = static_cast<Real *>(pa.drift0);
+    Real *__restrict__ frozen = static_cast<Real *>(pa.frozen);
+    Real *__restrict__ dt_t = static_cast<Real *>(pa.dt);
     __shared__ double es[LLL_N_MAX_MP * kQ];   // E, then W E R, by [rate][node]
     __shared__ double kap[LLL_N_MAX_MP];
     const int k = blockIdx.x, t = threadIdx.x;
@@ -495,20 +534,21 @@ __global__ void __launch_bounds__(64) full_tables_kernel(
 }
 
 template <typename Real>
-hipError_t launch_precompute_t(const lll_plan &p, hipStream_t st) {
-    const DeviceTables &d = p.d;
-    hipLaunchKernelGGL(setup_rule_kernel<Real>, dim3(p.N), dim3(kRuleBlock), 0, st, d.tenor,
-                       d.delta, d.L0, d.vol, p.N, p.s, p.off, p.driver, p.alpha, p.beta,
-                       p.delta_nig, p.c, d.x, d.w, d.steps, d.lam_pm, static_cast<Real *>(d.cinv),
-                       d.L0s, d.deltas, p.nmax, d.gx, d.gw, d.nq);
+hipError_t launch_setup(const PassArgs &one, const PassArgs *many, int structures, int max_N,
+                        int max_K, hipStream_t st) {
+    hipLaunchKernelGGL(setup_rule_kernel<Real>, dim3(max_N, structures), dim3(kRuleBlock), 0, st,
+                       one, many);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(setup_tables_kernel<Real>, dim3(p.K), dim3(256), 0, st, d.tenor, d.delta,
-                       d.L0, d.vol, d.gx, d.gw, d.nq, p.N, p.s, p.off, p.nmax, p.driver, p.alpha,
-                       p.beta, p.delta_nig, p.c, d.kappa, static_cast<Real *>(d.ew),
-                       static_cast<Real *>(d.lam), static_cast<Real *>(d.drift0),
-                       static_cast<Real *>(d.frozen), static_cast<Real *>(d.dt));
-    e = hipGetLastError();
+    hipLaunchKernelGGL(setup_tables_kernel<Real>, dim3(max_K, structures), dim3(256), 0, st, one,
+                       many);
+    return hipGetLastError();
+}
+
+template <typename Real>
+hipError_t launch_precompute_t(const lll_plan &p, hipStream_t st) {
+    const DeviceTables &d = p.d;
+    hipError_t e = launch_setup<Real>(pass_args(p), nullptr, 1, p.N, p.K, st);
     if (e != hipSuccess || !d.E) return e;
     hipLaunchKernelGGL(full_tables_kernel, dim3(p.K), dim3(64), 0, st, d.delta, d.L0, d.vol, d.x,
                        d.w, d.kappa, p.N, p.s, p.driver, p.c, d.E, d.b0);
@@ -588,6 +628,11 @@ hipError_t launch_set_inputs(const lll_plan &p, const double *L0_dev, const doub
 hipError_t launch_precompute(const lll_plan &p, hipStream_t st) {
     return p.precision == LLL_FP64 ? launch_precompute_t<double>(p, st)
                                    : launch_precompute_t<float>(p, st);
+}
+
+hipError_t launch_precompute_batch(const PassArgs *many, int structures, int max_N, int max_K,
+                                   hipStream_t st) {
+    return launch_setup<float>(PassArgs{}, many, structures, max_N, max_K, st);
 }
 
 }  // namespace lll
