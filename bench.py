@@ -505,8 +505,7 @@ def bench_maturity_parallel(lll, stream) -> dict:
                     ms.append(plan.timing()["paths"])
                 t = float(np.median(ms)) / 1e3
                 prices[name] = plan.results(stream)["price"]
-                fl = (flops_per_path(ts, "picard") if name == "picard_mp"  # on the 64 nodes
-                      else flops_per_path(ts, name, nodes)) * n
+                fl = flops_per_path(ts, "picard" if name == "picard_mp" else name, nodes) * n
                 res[name] = {"ms": t * 1e3, "path_steps_per_s": n * ts.n_steps / t,
                              "fp32_tflops": fl / t / 1e12, "frac_fp32_peak": fl / t / PEAK_FP32}
         for ref in ("picard", "full"):

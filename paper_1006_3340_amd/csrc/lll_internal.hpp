@@ -45,11 +45,8 @@ struct DeviceTables {
     void *kex = nullptr;       // exact-drift cumulant table (allocated on first use)
     void *xex = nullptr;       // [N][max_paths] exact-drift path states (allocated on first use)
     // maturity-parallel PICARD (FP32, allocated on first use)
-    void *mp_ewq = nullptr;       // [K][N][Q] (E, W E dt)
-    float *mp_ell = nullptr;      // [chunk/4][s N (N+1)/2][4] ell at the predictor, live rates
-    float *mp_z = nullptr;        // [chunk/4][N][N][4] per-period state increments
-    double *mp_pay = nullptr;     // [N][S+1][chunk] per-path payoff values
-    float *mp_dh = nullptr;       // [chunk/4][K][4] driver increments
+    float *mp_rec = nullptr;      // [K][N] records of the step tables
+    float *mp_x1 = nullptr;       // [chunk] predictor, Z and increments (picard_mp.hip)
     double *L0s = nullptr, *deltas = nullptr;   // [nmax] FP64 slot layout
     // reduction
     double *partials = nullptr;  // [max_waves][N][NSTAT]

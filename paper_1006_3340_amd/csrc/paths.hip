@@ -86,27 +86,29 @@ __global__ void __launch_bounds__(kBlock) sampler_math_kernel(int fn, const doub
 
 constexpr int kReduceBlock = 1024;
 constexpr int kChunkRows = 256;     // wavefronts per chunk row
+constexpr int kChunkCols = 256;     // columns per block of pass 1
+constexpr int kDirectRows = 32;     // up to here pass 2 reads the wave partials itself
 constexpr int kMaxCols = LLL_N_MAX_MP * (3 * LLL_S_MAX + 2);
 
-// Sums of rows r0 .. r1 of each of the cols columns, by column, into `out`: as
+// Sums of rows r0 .. r1 of the columns c_first .. c_end (of cols), into `out`: as
 // many row groups as the block holds of the padded columns, each group's rows in
 // order, then the groups in order (a fixed order whatever the grid).  The groups
 // and the unrolled loads hide the memory latency that one thread per column and
 // one row at a time left open (both passes and the results at N = 20, 2^20 paths:
 // 86 us, now 18).
 __device__ __forceinline__ void sum_rows(const double *__restrict__ in, int64_t r0, int64_t r1,
-                                         int cols, double *__restrict__ part,
-                                         double *__restrict__ out) {
-    const int width = min(kReduceBlock, (cols + 63) / 64 * 64);
+                                         int cols, int c_first, int c_end,
+                                         double *__restrict__ part, double *__restrict__ out) {
+    const int width = min(kReduceBlock, (c_end - c_first + 63) / 64 * 64);
     const int groups = kReduceBlock / width;
     const int g = threadIdx.x / width, c0 = threadIdx.x % width;
     const int64_t per = (r1 - r0 + groups - 1) / groups;
     const int64_t a = min(r1, r0 + g * per), b = min(r1, a + per);
-    for (int base = 0; base < cols; base += width) {
+    for (int base = c_first; base < c_end; base += width) {
         const int c = base + c0;
         if (g < groups) {
             double acc = 0.0;
-            if (c < cols) {
+            if (c < c_end) {
                 const double *p = in + a * cols + c;
                 int64_t r = a;
                 for (; r + 8 <= b; r += 8) {
@@ -122,7 +124,7 @@ __device__ __forceinline__ void sum_rows(const double *__restrict__ in, int64_t 
             part[threadIdx.x] = acc;
         }
         __syncthreads();
-        if (g == 0 && c < cols) {
+        if (g == 0 && c < c_end) {
             double acc = part[c0];
             for (int i = 1; i < groups; ++i) acc += part[i * width + c0];
             out[c] = acc;
@@ -131,7 +133,8 @@ __device__ __forceinline__ void sum_rows(const double *__restrict__ in, int64_t 
     }
 }
 
-// Pass 1: block b sums the wave partials' rows [b*256, (b+1)*256).
+// Pass 1: block b sums the wave partials' rows [b*256, (b+1)*256) of the 256
+// columns of blockIdx.z.
 __global__ void __launch_bounds__(kReduceBlock) reduce_rows_kernel(
     PassArgs one, const PassArgs *__restrict__ many, int64_t rows) {
     __shared__ double part[kReduceBlock];
@@ -139,12 +142,13 @@ __global__ void __launch_bounds__(kReduceBlock) reduce_rows_kernel(
     if (many) a = many[blockIdx.y];
     const int cols = a.N * (3 * a.S + 2);
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kChunkRows;
-    sum_rows(a.partials, r0, min(rows, r0 + kChunkRows), cols, part,
+    const int c0 = blockIdx.z * kChunkCols;
+    if (c0 >= cols) return;
+    sum_rows(a.partials, r0, min(rows, r0 + kChunkRows), cols, c0, min(cols, c0 + kChunkCols), part,
              a.chunks + static_cast<int64_t>(blockIdx.x) * cols);
 }
 
-// Pass 2: one block sums the chunk rows (or the wave partials themselves, up to
-// one chunk of them), then prices, standard errors and martingale residuals from
+// Pass 2: one block sums the chunk rows (or the few wave partials themselves), then prices, standard errors and martingale residuals from
 // the sums (eq. (caplet)): price = delta_i B(0, T_*) mean(p), B(0, T_*) =
 // B(0, T_1) / prod_l (1 + delta_l L_l(0)).
 __global__ void __launch_bounds__(kReduceBlock) finalize_kernel(PassArgs one,
@@ -157,7 +161,7 @@ __global__ void __launch_bounds__(kReduceBlock) finalize_kernel(PassArgs one,
     const int N = a.N, S = a.S, nstat = 3 * S + 2, cols = N * nstat;
     const int t = threadIdx.x;
     if (t < N) fac[t] = 1.0 + a.delta[t] * a.L0[t];
-    sum_rows(from_partials ? a.partials : a.chunks, 0, rows, cols, part, sums);
+    sum_rows(from_partials ? a.partials : a.chunks, 0, rows, cols, 0, cols, part, sums);
     for (int i = t; i < cols; i += kReduceBlock) a.sums[i] = sums[i];
     // inputs set from device memory that fail the checks of Section 2 give NaN
     const double poison = (a.lam_pm[2] != 0.0 || a.lam_pm[3] != 0.0) ? __builtin_nan("") : 0.0;
@@ -191,18 +195,22 @@ __global__ void __launch_bounds__(kReduceBlock) finalize_kernel(PassArgs one,
     }
 }
 
-hipError_t reduce(const PassArgs &one, const PassArgs *many, int structures, int64_t n_paths,
-                  hipStream_t st) {
+// max_cols: the most columns of any structure.
+hipError_t reduce(const PassArgs &one, const PassArgs *many, int structures, int max_cols,
+                  int64_t n_paths, hipStream_t st) {
     const int64_t waves = (n_paths + kWave - 1) / kWave;
     const int64_t chunks = (waves + kChunkRows - 1) / kChunkRows;
-    if (chunks > 1) {
-        hipLaunchKernelGGL(reduce_rows_kernel, dim3(static_cast<unsigned>(chunks), structures),
+    const bool direct = waves <= kDirectRows;
+    if (!direct) {
+        hipLaunchKernelGGL(reduce_rows_kernel,
+                           dim3(static_cast<unsigned>(chunks), structures,
+                                (max_cols + kChunkCols - 1) / kChunkCols),
                            dim3(kReduceBlock), 0, st, one, many, waves);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(finalize_kernel, dim3(1, structures), dim3(kReduceBlock), 0, st, one, many,
-                       chunks > 1 ? chunks : waves, chunks > 1 ? 0 : 1, n_paths);
+                       direct ? waves : chunks, direct ? 1 : 0, n_paths);
     return hipGetLastError();
 }
 
@@ -305,12 +313,12 @@ PassArgs pass_args(const lll_plan &p) {
 }
 
 hipError_t launch_reduce(const lll_plan &p, int64_t n_paths, hipStream_t st) {
-    return reduce(pass_args(p), nullptr, 1, n_paths, st);
+    return reduce(pass_args(p), nullptr, 1, p.N * (3 * p.S + 2), n_paths, st);
 }
 
 hipError_t launch_reduce_batch(const PassArgs *many, int structures, int64_t n_paths,
                                hipStream_t st) {
-    return reduce(PassArgs{}, many, structures, n_paths, st);
+    return reduce(PassArgs{}, many, structures, LLL_N_MAX * (3 * LLL_S_MAX + 2), n_paths, st);
 }
 
 hipError_t launch_increments(const lll_plan &p, int k, int64_t p0, int64_t n, uint64_t seed,
