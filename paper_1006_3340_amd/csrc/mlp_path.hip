@@ -47,6 +47,7 @@ using detail::PathArgs;
 
 constexpr int kSlots = kRates;  // the surrogate runs in the 40-slot bucket
 constexpr int kNStat = 8;
+constexpr int kResidentWaves = 2048;  // 256 CUs x 4 SIMDs x 2 wavefronts of this kernel
 constexpr int kLd = 72;         // padded row length (BF16) of the LDS tiles
 
 struct MlpArgs {
@@ -205,7 +206,14 @@ __device__ __forceinline__ void layer2(const __bf16 *Wp, int lane, const bf16x8 
 // Two wavefronts per SIMD (256 registers each, two 65 KiB blocks per CU): left
 // to itself the compiler takes ~300 registers and one wavefront per SIMD,
 // which ran the pass 1.6x slower at 2^20 paths.
-template <int SCHEME>
+//
+// SPLIT > 1: that many wavefronts of the block carry the same 64 paths.  All of
+// them draw, step and price the paths (the same arithmetic, so the same states);
+// each evaluates the network for every SPLIT-th coupled rate of a step, and they
+// exchange the outputs through their state tiles, which are free between the last
+// rate and the next step.  A pass too small to give every SIMD its two wavefronts
+// runs that much more of the network at once (see launch_mlp_paths).
+template <int SCHEME, int SPLIT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
     // 65 KiB: three padded weight tiles and the output unit's A operand
@@ -231,17 +239,23 @@ mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
                                             : static_cast<__bf16>(0.0f);
     }
     __syncthreads();  // the only block-wide barrier: the weights are read-only after it
-    const int64_t gid = static_cast<int64_t>(blockIdx.x) * kBlock + tid;
     const int lane = tid % kWave;
     const int grp = lane / 16;
-    const int64_t wave = gid / kWave;
-    if (gid - lane >= a.n_paths) return;  // whole wavefront past the end
+    constexpr int kSets = kBlock / kWave / SPLIT;  // sets of 64 paths in the block
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int part = wv % SPLIT;
+    const int64_t wave = static_cast<int64_t>(blockIdx.x) * kSets + wv / SPLIT;
+    const int64_t gid = wave * kWave + lane;
+    // whole wavefront past the end; with SPLIT > 1 it stays for the block's barriers
+    // and simulates paths that count nowhere
+    if (SPLIT == 1 && gid - lane >= a.n_paths) return;
     const bool active = gid < a.n_paths;
     const bool judge = g.judge_stride > 0 && (wave % g.judge_stride) == 0;
     const int64_t p = a.path_offset + gid;
     const uint32_t p_lo = static_cast<uint32_t>(p);
     const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(p) >> 32);
-    __bf16 *F = Ft[tid / kWave];
+    __bf16 *F = Ft[wv];
+    constexpr int kOwn = (kSlots - 1 + SPLIT - 1) / SPLIT;  // coupled rates of one part
     float X[kSlots];
 #pragma unroll
     for (int j = 0; j < kSlots; ++j) X[j] = 0.0f;
@@ -281,7 +295,16 @@ mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
             const float *B1k = g.B1 + (size_t)k * kRates * kHid;
             // rates in ascending slot order: after rate j the tile's column j + 1
             // is zeroed, so rate j + 1 reads exactly the states l > j + 1
-            for (int j = j0; j < kSlots - 1; ++j) {
+            float own[kOwn];
+            if constexpr (SPLIT > 1) {
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i) own[i] = 0.0f;
+                // a part starts at its first rate: the columns up to it are zero
+                for (int c = j0 + 1; c <= j0 + part && c < kSlots; ++c)
+                    F[lane * kLd + c] = static_cast<__bf16>(0.0f);
+                wave_sync();
+            }
+            for (int j = j0 + part; j < kSlots - 1; j += SPLIT) {
                 const int r = j - a.off;
                 float mine = 0.0f;
 #pragma unroll 1
@@ -330,18 +353,43 @@ mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
                         mine = (grp == 2 * np + t) ? (out[t][0] + out[t][1]) + out[t][2] : mine;
                 }
                 const float sy = g.sigma * (g.wf[kOffB4] + mine);
+                if constexpr (SPLIT == 1) {
 #pragma unroll
-                for (int jj = 0; jj < kSlots - 1; ++jj) C[jj] += (jj == j) ? sy : 0.0f;
-                // the next rate's features leave out this lane's state at column j + 1
-                F[lane * kLd + j + 1] = static_cast<__bf16>(0.0f);
+                    for (int jj = 0; jj < kSlots - 1; ++jj) C[jj] += (jj == j) ? sy : 0.0f;
+                } else {
+                    const int at = (j - j0) / SPLIT;
+#pragma unroll
+                    for (int i = 0; i < kOwn; ++i) own[i] = (i == at) ? sy : own[i];
+                }
+                // the next rate's features leave out this lane's states up to its column
+#pragma unroll
+                for (int c = 1; c <= SPLIT; ++c)
+                    if (j + c < kSlots) F[lane * kLd + j + c] = static_cast<__bf16>(0.0f);
                 wave_sync();
+            }
+            if constexpr (SPLIT > 1) {
+                static_assert(kOwn * sizeof(float) <= kLd * sizeof(__bf16), "outputs fit the tile");
+                float *mine_out = reinterpret_cast<float *>(F);
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i) mine_out[i * kWave + lane] = own[i];
+                __syncthreads();
+                const int set = wv / SPLIT * SPLIT;
+#pragma unroll
+                for (int jj = 0; jj < kSlots - 1; ++jj) {
+                    const int d = jj - j0;  // uniform
+                    if (d >= 0)
+                        C[jj] += reinterpret_cast<const float *>(
+                            Ft[set + d % SPLIT])[(d / SPLIT) * kWave + lane];
+                }
+                __syncthreads();  // the tiles are the states' again
             }
         }
         const bool need_quad = judge || __any((oob >> (j0 + 1)) != 0);
         dispatch_finish(std::make_integer_sequence<int, kSlots>{}, j0, a, k, dH, need_quad, judge,
                         oob, C, X, st);
         if (++js == a.s) {
-            detail::dispatch_payoff<float, kSlots, detail::kAnyProduct>(std::make_integer_sequence<int, kSlots>{}, j0, a,
+            if (SPLIT == 1 || (part == 0 && gid - lane < a.n_paths))
+                detail::dispatch_payoff<float, kSlots, detail::kAnyProduct>(std::make_integer_sequence<int, kSlots>{}, j0, a,
                                                    m, gid, active, X);
             js = 0;
             ++m;
@@ -354,7 +402,7 @@ mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
     tot[5] = mx;
-    if (lane == 0)
+    if (lane == 0 && part == 0 && gid < a.n_paths)
         for (int i = 0; i < kNStat; ++i) g.stats[wave * kNStat + i] = tot[i];
 }
 
@@ -420,8 +468,18 @@ hipError_t launch_mlp_paths(const lll_plan &p, const float *wts, const __bf16 *w
     g.sigma = sigma;
     g.use_net = use_net;
     g.judge_stride = judge_stride;
-    const dim3 grid(static_cast<unsigned>((n_paths + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL(mlp_path_kernel<kFull>, grid, dim3(kBlock), 0, st, a, g);
+    // wavefronts per 64 paths: as many as keep within the 2048 that the GPU holds (two
+    // per SIMD)
+    const int64_t waves = (n_paths + kWave - 1) / kWave;
+    const int split = !use_net || 2 * waves > kResidentWaves ? 1 : 4 * waves > kResidentWaves ? 2 : 4;
+    const int sets = kBlock / kWave / split;
+    const dim3 grid(static_cast<unsigned>((waves + sets - 1) / sets));
+    if (split == 1)
+        hipLaunchKernelGGL((mlp_path_kernel<kFull, 1>), grid, dim3(kBlock), 0, st, a, g);
+    else if (split == 2)
+        hipLaunchKernelGGL((mlp_path_kernel<kFull, 2>), grid, dim3(kBlock), 0, st, a, g);
+    else
+        hipLaunchKernelGGL((mlp_path_kernel<kFull, 4>), grid, dim3(kBlock), 0, st, a, g);
     return hipGetLastError();
 }
 
