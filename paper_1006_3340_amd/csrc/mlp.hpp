@@ -34,6 +34,7 @@ constexpr int kOffB3 = kOffW3 + kHid * kHid;
 constexpr int kOffW4 = kOffB3 + kHid;
 constexpr int kOffB4 = kOffW4 + kHid;
 constexpr int kParams = kOffB4 + 1;  // 14593
+constexpr int kGradRow = (kParams + 31) / 32 * 32;  // a block's gradients, on cache lines
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));

@@ -22,13 +22,11 @@ hipError_t launch_stats(const lll_plan &p, const float *states, const int *kidx,
                         const float *label, int64_t n_pairs, float *out, hipStream_t st);
 hipError_t launch_init(float *wts, __bf16 *wbf, float *adam, uint64_t seed, hipStream_t st);
 hipError_t launch_refresh(const float *wts, __bf16 *wbf, hipStream_t st);
-hipError_t launch_tiles(const __bf16 *feat, const float *target, const int *idx, int B,
-                        float inv_sigma, const float *wts, const __bf16 *wbf, float *gpart,
+hipError_t launch_tiles(const __bf16 *feat, const float *target, int64_t n_pairs, uint32_t step,
+                        uint64_t seed, int B, float inv_sigma, const float *wts, const __bf16 *wbf, float *gpart,
                         float *lpart, float *yout, float *loss_out, float *wts_mut,
                         __bf16 *wbf_mut, float *adam, float *grad_out, float lr, float bc1,
                         float bc2, hipStream_t st);
-hipError_t launch_batch_index(int *idx, int B, int64_t n_pairs, uint32_t step, uint64_t seed,
-                              hipStream_t st);
 hipError_t launch_mlp_tables(const lll_plan &p, const float *wts, float *K2, float *B1,
                              hipStream_t st);
 hipError_t launch_mlp_paths(const lll_plan &p, const float *wts, const __bf16 *wbf,
@@ -77,7 +75,6 @@ struct lll_mlp {
     float info_host[2 * kRates + 1] = {};
     bool have_data = false;
     // training scratch
-    int *idx = nullptr;
     float *gpart = nullptr, *lpart = nullptr, *loss = nullptr;
     int batch_cap = 0, loss_cap = 0;
 };
@@ -104,14 +101,12 @@ void free_data(lll_mlp *m) {
 int ensure_train_scratch(lll_mlp *m, int batch, int n_steps) {
     hipError_t e = hipSuccess;
     if (batch > m->batch_cap) {
-        if (m->idx) (void)hipFree(m->idx);
         if (m->gpart) (void)hipFree(m->gpart);
         if (m->lpart) (void)hipFree(m->lpart);
-        m->idx = nullptr;
         m->gpart = m->lpart = nullptr;
+        m->batch_cap = 0;
         const int tiles = (batch + 63) / 64;
-        e = hipMalloc(&m->idx, sizeof(int) * batch);
-        if (e == hipSuccess) e = hipMalloc(&m->gpart, sizeof(float) * (size_t)tiles * kParams);
+        e = hipMalloc(&m->gpart, sizeof(float) * (size_t)tiles * kGradRow);
         if (e == hipSuccess) e = hipMalloc(&m->lpart, sizeof(float) * tiles);
         if (e != hipSuccess) return fail(LLL_ENOMEM, "training scratch: %s", hipGetErrorString(e));
         m->batch_cap = batch;
@@ -133,7 +128,7 @@ extern "C" {
 int lll_mlp_destroy(lll_mlp *m) {
     if (!m) return LLL_OK;
     free_data(m);
-    void *ptrs[] = {m->wts, m->wbf, m->adam, m->info, m->idx, m->gpart, m->lpart, m->loss};
+    void *ptrs[] = {m->wts, m->wbf, m->adam, m->info, m->gpart, m->lpart, m->loss};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete m;
@@ -327,11 +322,9 @@ int lll_mlp_train(lll_mlp *m, int n_steps, int batch, float lr, uint64_t seed, f
         const int64_t tt = ++m->adam_steps;
         const float bc1 = static_cast<float>(1.0 / (1.0 - std::pow(0.9, (double)tt)));
         const float bc2 = static_cast<float>(1.0 / (1.0 - std::pow(0.999, (double)tt)));
-        e = launch_batch_index(m->idx, batch, m->n_pairs, static_cast<uint32_t>(tt), seed, st);
-        if (e == hipSuccess)
-            e = launch_tiles(m->feat, m->label, m->idx, batch, inv_sigma, m->wts, m->wbf, m->gpart,
-                             m->lpart, nullptr, m->loss + t, m->wts, m->wbf, m->adam, nullptr,
-                             lr_t, bc1, bc2, st);
+        e = launch_tiles(m->feat, m->label, m->n_pairs, static_cast<uint32_t>(tt), seed, batch,
+                         inv_sigma, m->wts, m->wbf, m->gpart, m->lpart, nullptr, m->loss + t,
+                         m->wts, m->wbf, m->adam, nullptr, lr_t, bc1, bc2, st);
     }
     if (e == hipSuccess && loss_host)
         e = hipMemcpyAsync(loss_host, m->loss, sizeof(float) * n_steps, hipMemcpyDeviceToHost, st);
@@ -361,11 +354,9 @@ int lll_mlp_train_dev(lll_mlp *m, const uint16_t *feat_dev, const float *label_d
         const int64_t tt = ++m->adam_steps;
         const float bc1 = static_cast<float>(1.0 / (1.0 - std::pow(0.9, (double)tt)));
         const float bc2 = static_cast<float>(1.0 / (1.0 - std::pow(0.999, (double)tt)));
-        e = launch_batch_index(m->idx, batch, n_pairs, static_cast<uint32_t>(tt), seed, st);
-        if (e == hipSuccess)
-            e = launch_tiles(feat, label_dev, m->idx, batch, 1.0f / sigma, m->wts, m->wbf, m->gpart,
-                             m->lpart, nullptr, loss + t, m->wts, m->wbf, m->adam, nullptr, lr_t,
-                             bc1, bc2, st);
+        e = launch_tiles(feat, label_dev, n_pairs, static_cast<uint32_t>(tt), seed, batch,
+                         1.0f / sigma, m->wts, m->wbf, m->gpart, m->lpart, nullptr, loss + t,
+                         m->wts, m->wbf, m->adam, nullptr, lr_t, bc1, bc2, st);
     }
     if (e != hipSuccess) return hip_fail(e, "training");
     return LLL_OK;
@@ -414,7 +405,7 @@ int lll_mlp_eval(lll_mlp *m, const float *feat_host, const float *target_host, i
     if (e == hipSuccess) e = hipMalloc(&fb, sizeof(__bf16) * n * kIn);
     if (e == hipSuccess) e = hipMalloc(&tgt, sizeof(float) * n);
     if (e == hipSuccess) e = hipMalloc(&y, sizeof(float) * n);
-    if (e == hipSuccess) e = hipMalloc(&gp, sizeof(float) * (size_t)tiles * kParams);
+    if (e == hipSuccess) e = hipMalloc(&gp, sizeof(float) * (size_t)tiles * kGradRow);
     if (e == hipSuccess) e = hipMalloc(&lp, sizeof(float) * tiles);
     if (e == hipSuccess) e = hipMalloc(&gout, sizeof(float) * kParams);
     if (e == hipSuccess) e = hipMalloc(&lout, sizeof(float));
@@ -429,7 +420,7 @@ int lll_mlp_eval(lll_mlp *m, const float *feat_host, const float *target_host, i
     }
     const bool grads = target_host != nullptr;
     if (e == hipSuccess)
-        e = launch_tiles(fb, grads ? tgt : y, nullptr, static_cast<int>(n), 1.0f, m->wts, m->wbf,
+        e = launch_tiles(fb, grads ? tgt : y, 0, 0u, 0, static_cast<int>(n), 1.0f, m->wts, m->wbf,
                          grads ? gp : nullptr, grads ? lp : nullptr, y, grads ? lout : nullptr,
                          m->wts, m->wbf, m->adam, gout, 0.0f, 1.0f, 1.0f, st);
     if (e == hipSuccess && y_host)

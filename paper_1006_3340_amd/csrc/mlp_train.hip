@@ -7,9 +7,9 @@
 //     (C_i - C'_i), C_i = sum_q W_q E_{i,q} (prod_{l>i}(1 + ell_l E_{l,q}) - 1)
 // (the quadrature coupling of eq. (LIBOR-drift-PT)) and C'_i its first-order
 // expansion (eq. (drifta)).  Training: minibatches drawn with replacement by
-// Philox (tag 2); one block of 256 threads per 64 samples runs the three
-// hidden layers forward and backward on v_mfma_f32_16x16x32_bf16 and writes
-// its gradient; a second kernel sums the block gradients in a fixed order and
+// Philox (tag 2); one block of eight wavefronts per 64 samples draws its rows, runs
+// the three hidden layers forward and backward on v_mfma_f32_16x16x32_bf16 and
+// writes its gradient; a second kernel sums the block gradients in a fixed order and
 // applies Adam to the FP32 master weights, refreshing their BF16 copies.
 #include <hip/hip_runtime.h>
 
@@ -28,8 +28,8 @@ namespace {
 using detail::cptr;
 using detail::PathArgs;
 
-constexpr int kTile = 64;      // samples per block
-constexpr int kTrainBlock = 256;
+constexpr int kTile = 64;         // samples per block
+constexpr int kTrainBlock = 512;  // eight wavefronts
 
 // ---------------------------------------------------------------- data ----
 
@@ -192,245 +192,298 @@ __global__ void __launch_bounds__(256) init_kernel(float *__restrict__ wts, __bf
     adam[kParams + p] = 0.0f;
 }
 
-__global__ void __launch_bounds__(256) batch_index_kernel(int *__restrict__ idx, int B,
-                                                          int64_t n_pairs, uint32_t step,
-                                                          uint32_t key0, uint32_t key1) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= B) return;
-    const uint4 r = philox4x32_10(make_uint4(step, static_cast<uint32_t>(j), 1u, 2u << 24), key0, key1);
-    const uint64_t x = (static_cast<uint64_t>(r.x) << 32) | r.y;
-    idx[j] = static_cast<int>(x % static_cast<uint64_t>(n_pairs));
-}
-
 struct TileArgs {
     const __bf16 *feat;   // [P][96]
     const float *target;  // [P] raw labels (scaled by inv_sigma here)
-    const int *idx;       // [B] sample indices, or null for rows 0..B-1
     int B;
+    uint64_t n_pairs;     // rows drawn with replacement among these, or 0: rows 0..B-1
+    uint64_t n_inv;       // floor((2^64 - 1) / n_pairs)
+    uint32_t step, key0, key1;
     float inv_sigma;
     float inv_B;
     const __bf16 *wbf;    // BF16 copy of the parameter vector
     const float *wf;      // FP32 parameter vector
-    float *gpart;         // [tiles][kParams] or null (forward only)
+    float *gpart;         // [tiles][kGradRow] or null (forward only)
     float *lpart;         // [tiles] loss partials or null
     float *yout;          // [B] outputs (normalised units) or null
 };
 
-__device__ __forceinline__ bf16x8 frag_contig(const __bf16 *p) {
-    bf16x8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = p[e];
-    return v;
-}
-__device__ __forceinline__ bf16x8 frag_strided(const __bf16 *p, int stride) {
-    bf16x8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = p[e * stride];
-    return v;
-}
-__device__ __forceinline__ bf16x8 frag_f32_contig(const float *p) {
-    bf16x8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = static_cast<__bf16>(p[e]);
-    return v;
-}
-__device__ __forceinline__ bf16x8 frag_f32_strided(const float *p, int stride) {
-    bf16x8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = static_cast<__bf16>(p[e * stride]);
-    return v;
+// Row of the batch's sample r: x mod n_pairs for 64 Philox bits x, the quotient from
+// one high product (n_inv x >> 64 is at most 2 below it).
+__device__ __forceinline__ int64_t sample_row(const TileArgs &t, int64_t r) {
+    if (t.n_pairs == 0) return r;
+    const uint4 w = philox4x32_10(make_uint4(t.step, static_cast<uint32_t>(r), 1u, 2u << 24),
+                                  t.key0, t.key1);
+    const uint64_t x = (static_cast<uint64_t>(w.x) << 32) | w.y;
+    uint64_t m = x - __umul64hi(x, t.n_inv) * t.n_pairs;
+    if (m >= t.n_pairs) m -= t.n_pairs;
+    if (m >= t.n_pairs) m -= t.n_pairs;
+    return static_cast<int64_t>(m);
 }
 
-// One hidden layer forward for the block's 64 samples: Z^T = W . H^T (+ b),
-// wave w computes hidden units 16w .. 16w+15 for all 64 samples.
-template <int KIN>
-__device__ __forceinline__ void layer_fwd(const __bf16 *Ws, const __bf16 *Hin, const float *bias,
-                                          float *Zout, __bf16 *Hout) {
-    const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
-    floatx4 acc[4];
+// LDS rows: 8 elements of padding behind 64 or 96 BF16 (4 behind 64 floats) keep 16-byte
+// alignment and spread 16 consecutive rows over the banks.
+constexpr int kLd = kHid + 8, kLdX = kIn + 8, kLdF = kHid + 4;
+
+// Every matrix is kept in the order in which the product that takes it reads 8
+// contraction indices at once (16 bytes a lane): the activations and dZ by sample (for
+// the next layer and for dH) and by unit (for dW), W2 and W3 transposed for dH.
+struct TileLds {
+    union {
+        struct {
+            __bf16 X[kTile * kLdX];         // [m][i]
+            __bf16 H[2][kTile * kLd];       // [m][o], layers 1 and 2
+        } fwd;
+        float dZ[3][kTile * kLdF];          // [m][o], layers 1..3 (after the forward pass)
+    };
+    __bf16 XT[kIn * kLd];                   // [i][m]
+    __bf16 HT[2][kHid * kLd];               // [o][m]
+    __bf16 H3[kTile * kLd];                 // [m][o]
+    __bf16 WT[2][kHid * kLd];               // [i][o], layers 2 and 3
+    __bf16 dZb[2][kTile * kLd];             // [m][o], layers 2 and 3
+    __bf16 dZT[2][kHid * kLd];              // [o][m], layer l in slot l % 2
+    float dy[kTile], loss[kTile];
+};
+
+// 16 bytes of BF16 data with the alignment of the caller's features.
+struct __attribute__((packed, aligned(2))) Chunk {
+    uint32_t d[4];
+};
+__device__ __forceinline__ bf16x8 load_chunk(const __bf16 *p) {
+    const Chunk c = *reinterpret_cast<const Chunk *>(p);
+    return __builtin_bit_cast(bf16x8, c.d);
+}
+__device__ __forceinline__ bf16x8 frag(const __bf16 *p) {
+    return *reinterpret_cast<const bf16x8 *>(p);
+}
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// Wave w holds units 16 (w % 4) + 4 (lane / 16) + e of samples 32 (w / 4) + 16 j +
+// lane % 16, j = 0, 1, of every layer's Z, H, dH and dZ: what the matrix instruction
+// returns for Z^T = W H^T and dH^T = W^T dZ^T alike, so that Z stays in registers.
+struct Lane {
+    int ob, nb, lr, lk;  // 16 (w % 4), 32 (w / 4), lane % 16, lane / 16
+    __device__ int unit() const { return ob + 4 * lk; }
+    __device__ int sample(int j) const { return nb + 16 * j + lr; }
+};
+
+// Z^T = W . H^T + b for the wave's units and samples, W's rows in registers.
+template <int KT, int LD>
+__device__ __forceinline__ void layer_fwd(const Lane &l, const bf16x8 (&W)[KT], const __bf16 *Hin,
+                                          const floatx4 &bias, floatx4 (&Z)[2]) {
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int j = 0; j < 2; ++j) {
+        floatx4 acc{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int kt = 0; kt < KIN / 32; ++kt) {
-        const int k0 = 32 * kt + 8 * (lane / 16);
-        const bf16x8 a = frag_contig(Ws + (16 * w + lane % 16) * KIN + k0);
+        for (int kt = 0; kt < KT; ++kt)
+            acc = mfma16(W[kt], frag(Hin + l.sample(j) * LD + 32 * kt + 8 * l.lk), acc);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const bf16x8 b = frag_contig(Hin + (16 * nt + lane % 16) * KIN + k0);
-            acc[nt] = mfma16(a, b, acc[nt]);
-        }
+        for (int e = 0; e < 4; ++e) Z[j][e] = acc[e] + bias[e];
     }
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int o = 16 * w + 4 * (lane / 16) + e, m = 16 * nt + lane % 16;
-            const float z = acc[nt][e] + bias[o];
-            Zout[m * kHid + o] = z;
-            Hout[m * kHid + o] = static_cast<__bf16>(gelu(z));
-        }
 }
 
-// dW[o][i] = sum_m dZ[m][o] Hin[m][i] for the block; wave w rows o = 16w..,
-// NT column tiles of 16; written to the block's gradient slice.
-template <int NT, int HSTRIDE>
-__device__ __forceinline__ void weight_grad(const float *dZ, const __bf16 *Hin, float *g) {
-    const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
-    floatx4 acc[NT];
+// One wave's tile to its [m][o] and / or [o][m] copy.
+__device__ __forceinline__ void put(const Lane &l, int j, const floatx4 &v, __bf16 *rows,
+                                    __bf16 *cols) {
+    bf16x4 b;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int e = 0; e < 4; ++e) b[e] = static_cast<__bf16>(v[e]);
+    if (rows) *reinterpret_cast<bf16x4 *>(rows + l.sample(j) * kLd + l.unit()) = b;
+    if (cols)
 #pragma unroll
-    for (int kt = 0; kt < kTile / 32; ++kt) {
-        const int m0 = 32 * kt + 8 * (lane / 16);
-        const bf16x8 a = frag_f32_strided(dZ + m0 * kHid + 16 * w + lane % 16, kHid);
+        for (int e = 0; e < 4; ++e) cols[(l.unit() + e) * kLd + l.sample(j)] = b[e];
+}
+
+// dW[o][i] = sum_m dZ[m][o] Hin[m][i] for the block: the wave's 16 rows o and half of
+// the NT column tiles of 16, written to the block's gradient slice.
+template <int NT, int STRIDE>
+__device__ __forceinline__ void weight_grad(const Lane &l, const __bf16 *dZT, const __bf16 *HT,
+                                            float *g) {
+    const int first = l.nb / 32 * (NT / 2);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const bf16x8 b = frag_strided(Hin + m0 * HSTRIDE + 16 * nt + lane % 16, HSTRIDE);
-            acc[nt] = mfma16(a, b, acc[nt]);
-        }
+    for (int j = 0; j < NT / 2; ++j) {
+        floatx4 acc{0.0f, 0.0f, 0.0f, 0.0f};
+        const int i = 16 * (first + j) + l.lr;
+#pragma unroll
+        for (int kt = 0; kt < kTile / 32; ++kt)
+            acc = mfma16(frag(dZT + (l.ob + l.lr) * kLd + 32 * kt + 8 * l.lk),
+                         frag(HT + i * kLd + 32 * kt + 8 * l.lk), acc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[(l.unit() + e) * STRIDE + i] = acc[e];
     }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int o = 16 * w + 4 * (lane / 16) + e, i = 16 * nt + lane % 16;
-            g[o * HSTRIDE + i] = acc[nt][e];
-        }
 }
 
-// dH^T[i][m] = sum_o W[o][i] dZ[m][o]; returns the wave's 4 tiles
-// (i = 16w + 4(lane/16) + e, m = 16nt + lane%16).
-__device__ __forceinline__ void input_grad(const __bf16 *Ws, const float *dZ, floatx4 (&acc)[4]) {
-    const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
+// dZ of the layer below: (dH^T = W^T dZ^T) gelu'(Z).
+__device__ __forceinline__ void input_grad(const Lane &l, const __bf16 *WT, const __bf16 *dZb,
+                                           const floatx4 (&Z)[2], floatx4 (&dZ)[2]) {
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int j = 0; j < 2; ++j) {
+        floatx4 acc{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int kt = 0; kt < kHid / 32; ++kt)
+            acc = mfma16(frag(WT + (l.ob + l.lr) * kLd + 32 * kt + 8 * l.lk),
+                         frag(dZb + l.sample(j) * kLd + 32 * kt + 8 * l.lk), acc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dZ[j][e] = acc[e] * gelu_grad(Z[j][e]);
+    }
+}
+
+// Column sums over the block's samples, in sample order: one lane a unit.
+__device__ __forceinline__ float column_sum(const float *dZ, int o) {
+    float s = 0.0f;
+#pragma unroll 16
+    for (int m = 0; m < kTile; ++m) s += dZ[m * kLdF + o];
+    return s;
+}
+
+// A batch of 16384 is 256 blocks, one a compute unit: what bounds the kernel is the time
+// of one block, a chain of gathers, products and barriers.  So the rows are drawn here,
+// all loads are 16 bytes a lane and issued at once, W1..W3 go to registers as
+// fragments, eight wavefronts share the elementwise work, and the bias sums wait for
+// the end, one wavefront each.  At a batch of 16384: 16 us; with 2-byte loads, unpadded
+// rows read across, Z in LDS and four wavefronts 38 us and 4.6 us for the rows' own launch.
+__global__ void __launch_bounds__(kTrainBlock) tile_kernel(TileArgs t) {
+    __shared__ TileLds S;
+    const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
+    const Lane l{16 * (w % 4), 32 * (w / 4), lane % 16, lane / 16};
+    const __bf16 *wbf = t.wbf;
+    const float *wf = t.wf;
+    bf16x8 W1[kIn / 32], W2[kHid / 32], W3[kHid / 32], wt[2];
+#pragma unroll
+    for (int kt = 0; kt < kIn / 32; ++kt)
+        W1[kt] = load_chunk(wbf + kOffW1 + (l.ob + l.lr) * kIn + 32 * kt + 8 * l.lk);
 #pragma unroll
     for (int kt = 0; kt < kHid / 32; ++kt) {
-        const int o0 = 32 * kt + 8 * (lane / 16);
-        const bf16x8 a = frag_strided(Ws + o0 * kHid + 16 * w + lane % 16, kHid);
+        W2[kt] = load_chunk(wbf + kOffW2 + (l.ob + l.lr) * kHid + 32 * kt + 8 * l.lk);
+        W3[kt] = load_chunk(wbf + kOffW3 + (l.ob + l.lr) * kHid + 32 * kt + 8 * l.lk);
+    }
+    wt[0] = load_chunk(wbf + kOffW2 + lane * kHid + 8 * w);
+    wt[1] = load_chunk(wbf + kOffW3 + lane * kHid + 8 * w);
+    floatx4 b1, b2, b3, w4;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const bf16x8 b = frag_f32_contig(dZ + (16 * nt + lane % 16) * kHid + o0);
-            acc[nt] = mfma16(a, b, acc[nt]);
-        }
+    for (int e = 0; e < 4; ++e) {
+        b1[e] = wf[kOffB1 + l.unit() + e];
+        b2[e] = wf[kOffB2 + l.unit() + e];
+        b3[e] = wf[kOffB3 + l.unit() + e];
+        w4[e] = wf[kOffW4 + l.unit() + e];
     }
-}
-
-__global__ void __launch_bounds__(kTrainBlock) tile_kernel(TileArgs t) {
-    __shared__ __bf16 Xs[kTile * kIn];
-    __shared__ __bf16 W1s[kHid * kIn];
-    __shared__ __bf16 W2s[kHid * kHid];
-    __shared__ __bf16 W3s[kHid * kHid];
-    __shared__ __bf16 Hs[3][kTile * kHid];
-    __shared__ float Zs[3][kTile * kHid];
-    __shared__ float dZ[kTile * kHid];
-    __shared__ float dyS[kTile];
-    __shared__ float red[kTile];
-    const int tid = threadIdx.x;
-    const int lane = tid % 64, w = tid / 64;
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kTile;
-    const float *wf = t.wf;
-    for (int e = tid; e < kTile * kIn; e += kTrainBlock) {
-        const int m = e / kIn, c = e % kIn;
-        const int64_t r = row0 + m;
-        __bf16 v = static_cast<__bf16>(0.0f);
-        if (r < t.B) {
-            const int64_t smp = t.idx ? t.idx[r] : r;
-            v = t.feat[smp * kIn + c];
-        }
-        Xs[e] = v;
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * kTile + lane;
+    const bool valid = r < t.B;
+    float target = 0.0f;
+    bf16x8 x[2] = {};
+    if (valid) {
+        const int64_t smp = sample_row(t, r);
+        const __bf16 *row = t.feat + smp * kIn;
+        x[0] = load_chunk(row + 8 * w);
+        if (w < kIn / 8 - 8) x[1] = load_chunk(row + 64 + 8 * w);
+        if (w == 0) target = t.target[smp] * t.inv_sigma;
     }
-    for (int e = tid; e < kHid * kIn; e += kTrainBlock) W1s[e] = t.wbf[kOffW1 + e];
-    for (int e = tid; e < kHid * kHid; e += kTrainBlock) {
-        W2s[e] = t.wbf[kOffW2 + e];
-        W3s[e] = t.wbf[kOffW3 + e];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        if (c == 1 && w >= kIn / 8 - 8) break;
+        const int i = 64 * c + 8 * w;
+        *reinterpret_cast<bf16x8 *>(S.fwd.X + lane * kLdX + i) = x[c];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) S.XT[(i + e) * kLd + lane] = x[c][e];
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) S.WT[c][(8 * w + e) * kLd + lane] = wt[c][e];
+    __syncthreads();
+    floatx4 Z1[2], Z2[2], Z3[2], v;
+    auto activate = [&](const floatx4 &z) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = gelu(z[e]);
+    };
+    layer_fwd<kIn / 32, kLdX>(l, W1, S.fwd.X, b1, Z1);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        activate(Z1[j]);
+        put(l, j, v, S.fwd.H[0], S.HT[0]);
     }
     __syncthreads();
-    layer_fwd<kIn>(W1s, Xs, wf + kOffB1, Zs[0], Hs[0]);
+    layer_fwd<kHid / 32, kLd>(l, W2, S.fwd.H[0], b2, Z2);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        activate(Z2[j]);
+        put(l, j, v, S.fwd.H[1], S.HT[1]);
+    }
     __syncthreads();
-    layer_fwd<kHid>(W2s, Hs[0], wf + kOffB2, Zs[1], Hs[1]);
+    layer_fwd<kHid / 32, kLd>(l, W3, S.fwd.H[1], b3, Z3);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        activate(Z3[j]);
+        put(l, j, v, S.H3, nullptr);
+    }
     __syncthreads();
-    layer_fwd<kHid>(W3s, Hs[1], wf + kOffB3, Zs[2], Hs[2]);
-    __syncthreads();
-    if (tid < kTile) {
-        const int64_t r = row0 + tid;
-        const bool valid = r < t.B;
+    if (w == 0) {
         float y = wf[kOffB4];
-        for (int o = 0; o < kHid; ++o) y = fmaf(wf[kOffW4 + o], static_cast<float>(Hs[2][tid * kHid + o]), y);
-        float target = 0.0f;
-        if (valid) {
-            const int64_t smp = t.idx ? t.idx[r] : r;
-            target = t.target[smp] * t.inv_sigma;
-            if (t.yout) t.yout[r] = y;
+#pragma unroll
+        for (int c = 0; c < kHid / 8; ++c) {
+            const bf16x8 h = frag(S.H3 + lane * kLd + 8 * c);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                y = fmaf(wf[kOffW4 + 8 * c + e], static_cast<float>(h[e]), y);
         }
+        if (valid && t.yout) t.yout[r] = y;
         const float d = valid ? (y - target) : 0.0f;
-        dyS[tid] = d * t.inv_B;
-        red[tid] = 0.5f * d * d * t.inv_B;
+        S.dy[lane] = d * t.inv_B;
+        S.loss[lane] = 0.5f * d * d * t.inv_B;
     }
     __syncthreads();
-    if (t.lpart && tid == 0) {
+    if (t.lpart && w == 7 && lane == 0) {
         float s = 0.0f;
-        for (int m = 0; m < kTile; ++m) s += red[m];
+        for (int m = 0; m < kTile; ++m) s += S.loss[m];
         t.lpart[blockIdx.x] = s;
     }
     if (!t.gpart) return;
-    float *g = t.gpart + static_cast<int64_t>(blockIdx.x) * kParams;
-    // output layer and dZ3
-    if (tid < kHid) {
+    float *g = t.gpart + static_cast<int64_t>(blockIdx.x) * kGradRow;
+    floatx4 dZ[2];
+    auto put_f32 = [&](float *out) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            *reinterpret_cast<floatx4 *>(out + l.sample(j) * kLdF + l.unit()) = dZ[j];
+    };
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float dy = S.dy[l.sample(j)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dZ[j][e] = dy * w4[e] * gelu_grad(Z3[j][e]);
+        put(l, j, dZ[j], S.dZb[1], S.dZT[1]);
+    }
+    put_f32(S.dZ[2]);
+    __syncthreads();
+    input_grad(l, S.WT[1], S.dZb[1], Z2, dZ);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) put(l, j, dZ[j], S.dZb[0], S.dZT[0]);
+    put_f32(S.dZ[1]);
+    weight_grad<kHid / 16, kHid>(l, S.dZT[1], S.HT[1], g + kOffW3);
+    __syncthreads();
+    input_grad(l, S.WT[0], S.dZb[0], Z1, dZ);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) put(l, j, dZ[j], nullptr, S.dZT[1]);
+    put_f32(S.dZ[0]);
+    weight_grad<kHid / 16, kHid>(l, S.dZT[0], S.HT[0], g + kOffW2);
+    __syncthreads();
+    weight_grad<kIn / 16, kIn>(l, S.dZT[1], S.XT, g + kOffW1);
+    if (w == 0) {
+        g[kOffB1 + lane] = column_sum(S.dZ[0], lane);
+    } else if (w == 1) {
+        g[kOffB2 + lane] = column_sum(S.dZ[1], lane);
+    } else if (w == 2) {
+        g[kOffB3 + lane] = column_sum(S.dZ[2], lane);
+    } else if (w == 3) {
         float s = 0.0f;
-        for (int m = 0; m < kTile; ++m) s = fmaf(dyS[m], static_cast<float>(Hs[2][m * kHid + tid]), s);
-        g[kOffW4 + tid] = s;
-    } else if (tid == kHid) {
+#pragma unroll 16
+        for (int m = 0; m < kTile; ++m)
+            s = fmaf(S.dy[m], static_cast<float>(S.H3[m * kLd + lane]), s);
+        g[kOffW4 + lane] = s;
+    } else if (w == 4 && lane == 0) {
         float s = 0.0f;
-        for (int m = 0; m < kTile; ++m) s += dyS[m];
+        for (int m = 0; m < kTile; ++m) s += S.dy[m];
         g[kOffB4] = s;
-    }
-    for (int e = tid; e < kTile * kHid; e += kTrainBlock) {
-        const int m = e / kHid, o = e % kHid;
-        dZ[e] = dyS[m] * wf[kOffW4 + o] * gelu_grad(Zs[2][e]);
-    }
-    __syncthreads();
-    // layer 3: dW3, db3, dH2
-    weight_grad<4, kHid>(dZ, Hs[1], g + kOffW3);
-    if (tid < kHid) {
-        float s = 0.0f;
-        for (int m = 0; m < kTile; ++m) s += dZ[m * kHid + tid];
-        g[kOffB3 + tid] = s;
-    }
-    floatx4 acc[4];
-    input_grad(W3s, dZ, acc);
-    __syncthreads();
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 16 * w + 4 * (lane / 16) + e, m = 16 * nt + lane % 16;
-            dZ[m * kHid + i] = acc[nt][e] * gelu_grad(Zs[1][m * kHid + i]);
-        }
-    __syncthreads();
-    // layer 2: dW2, db2, dH1
-    weight_grad<4, kHid>(dZ, Hs[0], g + kOffW2);
-    if (tid < kHid) {
-        float s = 0.0f;
-        for (int m = 0; m < kTile; ++m) s += dZ[m * kHid + tid];
-        g[kOffB2 + tid] = s;
-    }
-    input_grad(W2s, dZ, acc);
-    __syncthreads();
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 16 * w + 4 * (lane / 16) + e, m = 16 * nt + lane % 16;
-            dZ[m * kHid + i] = acc[nt][e] * gelu_grad(Zs[0][m * kHid + i]);
-        }
-    __syncthreads();
-    // layer 1: dW1, db1
-    weight_grad<kIn / 16, kIn>(dZ, Xs, g + kOffW1);
-    if (tid < kHid) {
-        float s = 0.0f;
-        for (int m = 0; m < kTile; ++m) s += dZ[m * kHid + tid];
-        g[kOffB1 + tid] = s;
     }
 }
 
@@ -439,7 +492,8 @@ __global__ void __launch_bounds__(kTrainBlock) tile_kernel(TileArgs t) {
 // parameter's tiles are split into 8 contiguous slices summed by 8 threads at
 // once (coalesced rows of 32 parameters), then the slices in slice order: a
 // fixed summation order, the same in every call.  Block 0 sums the tile losses
-// the same way.
+// the same way.  256 tiles are 15 MB: 4.5 us with 16 loads of a slice in flight on whole
+// cache lines, 13.7 us with rows of an odd number of floats and few in flight.
 constexpr int kSlices = 8;
 constexpr int kParamsPerBlock = 256 / kSlices;
 
@@ -459,10 +513,12 @@ __global__ void __launch_bounds__(256) reduce_adam_kernel(const float *__restric
     const int t0 = sl * per, t1 = min(tiles, t0 + per);
     float s = 0.0f;
     if (p < kParams)
-        for (int i = t0; i < t1; ++i) s += gpart[static_cast<int64_t>(i) * kParams + p];
+#pragma unroll 16
+        for (int i = t0; i < t1; ++i) s += gpart[static_cast<int64_t>(i) * kGradRow + p];
     part[sl][pl] = s;
     if (blockIdx.x == 0 && loss_out && pl == 0) {
         float l = 0.0f;
+#pragma unroll 16
         for (int i = t0; i < t1; ++i) l += lpart[i];
         lsum[sl] = l;
     }
@@ -536,29 +592,25 @@ hipError_t launch_refresh(const float *wts, __bf16 *wbf, hipStream_t st) {
     return hipGetLastError();
 }
 
-// One pass over B samples: forward (and backward when gpart != null), then the
-// fixed-order reduction (and an Adam step when lr > 0).
-hipError_t launch_tiles(const __bf16 *feat, const float *target, const int *idx, int B,
-                        float inv_sigma, const float *wts, const __bf16 *wbf, float *gpart,
+// One pass over B samples (drawn among n_pairs rows by (seed, step), or rows 0..B-1
+// with n_pairs = 0): forward (and backward when gpart != null), then the fixed-order
+// reduction (and an Adam step when lr > 0).
+hipError_t launch_tiles(const __bf16 *feat, const float *target, int64_t n_pairs, uint32_t step,
+                        uint64_t seed, int B, float inv_sigma, const float *wts, const __bf16 *wbf, float *gpart,
                         float *lpart, float *yout, float *loss_out, float *wts_mut,
                         __bf16 *wbf_mut, float *adam, float *grad_out, float lr, float bc1,
                         float bc2, hipStream_t st) {
     const int tiles = (B + kTile - 1) / kTile;
-    TileArgs t{feat, target, idx, B, inv_sigma, 1.0f / static_cast<float>(B), wbf, wts, gpart,
-               lpart, yout};
+    const uint64_t n = static_cast<uint64_t>(n_pairs);
+    TileArgs t{feat, target, B, n, n ? ~uint64_t{0} / n : 0, step, static_cast<uint32_t>(seed),
+               static_cast<uint32_t>(seed >> 32), inv_sigma, 1.0f / static_cast<float>(B), wbf,
+               wts, gpart, lpart, yout};
     hipLaunchKernelGGL(tile_kernel, dim3(tiles), dim3(kTrainBlock), 0, st, t);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !gpart) return e;
     hipLaunchKernelGGL(reduce_adam_kernel, dim3((kParams + kParamsPerBlock - 1) / kParamsPerBlock),
                        dim3(256), 0, st, gpart,
                        tiles, lpart, loss_out, wts_mut, wbf_mut, adam, grad_out, lr, bc1, bc2);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_index(int *idx, int B, int64_t n_pairs, uint32_t step, uint64_t seed,
-                              hipStream_t st) {
-    hipLaunchKernelGGL(batch_index_kernel, dim3((B + 255) / 256), dim3(256), 0, st, idx, B,
-                       n_pairs, step, static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32));
     return hipGetLastError();
 }
 
