@@ -158,7 +158,7 @@ __device__ __forceinline__ void quad_coupling2(cptr<Real> row, int nq, const Rea
         for (int q = 0; q < nq; ++q, row += NMAX * 2) {
             Real t = ell[NMAX - 1] * row[2 * (NMAX - 1)];
             Real s = t;
-            Real u = Real(1) + t;
+            Real u = fma(ell[NMAX - 1], row[2 * (NMAX - 1)], Real(1));
 #pragma unroll
             for (int j = NMAX - 2; j >= J0; --j) {
                 const Real E = row[2 * j];
@@ -167,7 +167,7 @@ __device__ __forceinline__ void quad_coupling2(cptr<Real> row, int nq, const Rea
                 if (j > J0) {
                     t = ell[j] * E;
                     s = fma(t, u, s);
-                    u = u + t;
+                    u = fma(ell[j], E, u);
                 }
             }
         }
@@ -588,6 +588,14 @@ __global__ void __launch_bounds__(kBlock) drift_kernel(PathArgs<Real> a, int k,
                                L + i * a.N, kappa, b + i * a.N);
 }
 
+}  // namespace detail
+}  // namespace lll
+
+#include "quad_kernel.hpp"
+
+namespace lll {
+namespace detail {
+
 template <typename Real>
 inline PathArgs<Real> make_args(const lll_plan &p, uint64_t seed, int64_t n_paths, int64_t path_offset,
                          double *path_fix) {
@@ -628,6 +636,32 @@ size_t state_lds_bytes(const PathArgs<Real> &a) {
     return kStateInLds<Real, NMAX, SCHEME> ? size_t(a.N) * kBlock * sizeof(Real) : 0;
 }
 
+// Passes up to this many paths take four lanes a path (quad_kernel.hpp).  Both kernels
+// are flat in the path count until the chip's SIMDs are shared, quads up to 16,384 and the
+// wide kernel up to 131,072 paths, and then grow, quads four times as early: 200 steps of
+// 20 rates, FP32 FULL, 277 against 637 us at 4,000 paths, 513 against 620 at
+// 65,536, 758 against 620 at 100,000.  With 32 and 40 slots and in FP64 (1,160 against
+// 1,930 us at 32,768 paths and 40 rates, 2,190 against 1,920 at 65,536) two
+// wavefronts a SIMD are the most that fit, and the lines cross earlier, but not for FROZEN and
+// FIRST_ORDER, whose quads carry no recursion.
+template <typename Real, int NMAX>
+int64_t quad_limit(int scheme) {
+    return (sizeof(Real) == 4 && NMAX <= 24) || scheme == kFrozen || scheme == kFirst ? 65536 : 32768;
+}
+
+template <typename Real, int NMAX>
+hipError_t launch_quads(const PathArgs<Real> &a, int scheme, hipStream_t st) {
+    const dim3 grid(static_cast<unsigned>((a.n_paths + kQuadPaths - 1) / kQuadPaths));
+    switch (scheme) {
+        case kFull: hipLaunchKernelGGL((quad_kernel<Real, NMAX, kFull>), grid, dim3(kBlock), 0, st, a); break;
+        case kPicard: hipLaunchKernelGGL((quad_kernel<Real, NMAX, kPicard>), grid, dim3(kBlock), 0, st, a); break;
+        case kFirst: hipLaunchKernelGGL((quad_kernel<Real, NMAX, kFirst>), grid, dim3(kBlock), 0, st, a); break;
+        case kSecond: hipLaunchKernelGGL((quad_kernel<Real, NMAX, kSecond>), grid, dim3(kBlock), 0, st, a); break;
+        default: hipLaunchKernelGGL((quad_kernel<Real, NMAX, kFrozen>), grid, dim3(kBlock), 0, st, a); break;
+    }
+    return hipGetLastError();
+}
+
 template <typename Real, int NMAX, int PRODUCT, int SCHEME>
 void launch_one_scheme(const PathArgs<Real> &a, dim3 grid, hipStream_t st) {
     const size_t lds = state_lds_bytes<Real, NMAX, SCHEME>(a);
@@ -647,6 +681,7 @@ void launch_scheme(const PathArgs<Real> &a, int scheme, dim3 grid, hipStream_t s
 
 template <typename Real, int NMAX>
 hipError_t launch_paths_n(const PathArgs<Real> &a, int scheme, int64_t n_paths, hipStream_t st) {
+    if (n_paths <= quad_limit<Real, NMAX>(scheme)) return launch_quads<Real, NMAX>(a, scheme, st);
     const dim3 grid(static_cast<unsigned>((n_paths + kBlock - 1) / kBlock));
     if (a.product == LLL_SWAPTIONS)
         launch_scheme<Real, NMAX, LLL_SWAPTIONS>(a, scheme, grid, st);

@@ -444,12 +444,12 @@ __global__ void __launch_bounds__(256) setup_tables_kernel(PassArgs one,
         kap[t] = kv;
         kappa_out[(size_t)k * N + t] = kv;
     }
-    for (int i = t; i < nmax * nq; i += 256) {
+    for (int i = t; i < nmax * ((nq + 3) / 4 * 4); i += 256) {  // zero rows to a multiple of 4
         const int q = i / nmax, j = i % nmax, r = j - off;
-        const double E = (r >= m && nig) ? expm1(lam[r] * x[q]) : 0.0;
+        const double E = (r >= m && nig && q < nq) ? expm1(lam[r] * x[q]) : 0.0;
         Real *row = ew + (((size_t)k * kQ + q) * nmax + j) * 2;
         row[0] = static_cast<Real>(E);
-        row[1] = static_cast<Real>(w[q] * E);
+        row[1] = static_cast<Real>(q < nq ? w[q] * E : 0.0);
         if (r >= 0) es[r * kQ + q] = E;
     }
     __syncthreads();
