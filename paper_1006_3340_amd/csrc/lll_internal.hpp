@@ -22,6 +22,8 @@ constexpr int kQSize = 64;     // quadrature nodes
 int bucket_for(int n_rates, bool slots20);
 
 struct DeviceTables {
+    void *arena = nullptr;     // the one allocation that holds the buffers below but
+                               // E, vol_base, k2, kex, xex (null: not the plan's own)
     // FP64 inputs (device)
     double *tenor = nullptr, *delta = nullptr, *L0 = nullptr, *vol = nullptr, *strikes = nullptr;
     // FP64 precompute, inspection layout
