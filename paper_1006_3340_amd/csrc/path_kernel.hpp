@@ -435,6 +435,32 @@ __device__ __forceinline__ void dispatch_payoff(std::integer_sequence<int, Js...
     (void)((j0 == Js ? (payoff<Real, NMAX, Js, PRODUCT>(a, m, gid, active, X), 0) : 0) + ...);
 }
 
+// Brings a step's node rows into this XCD's L2 two steps before they are read: the first
+// wavefront of a block touches one 128-byte line a lane, and the value is dropped a step
+// later.  For rules of more than kTouchNodes nodes in FP32 plans of up to 16 slots, whose
+// rows are waited for one after the other: 9 rates, 45 steps, 24 to 5 nodes, SECOND_ORDER 316 ->
+// 260 us at 131,072 paths and 801 -> 766 at 2^20, FULL 305 -> 255.  With few nodes other
+// wavefronts cover the wait; with more slots (light tails: few nodes) and in FP64 the
+// registers cost a wavefront (PICARD at 40 rates +4%, FP64 SECOND_ORDER +13%).
+constexpr int kTouchNodes = 8;
+template <typename Real, int NMAX, int SCHEME>
+struct TableTouch {
+    uint32_t value = 0;
+    __device__ __forceinline__ void step(const PathArgs<Real> &a, int k, int K) {
+        if constexpr (sizeof(Real) == 4 && NMAX <= 16 &&
+                      (SCHEME == kFull || SCHEME == kPicard || SCHEME == kSecond)) {
+            const int next = min(k + 2, K - 1), nodes = a.nq[next];
+            if (nodes <= kTouchNodes || a.brownian || threadIdx.x >= kWave) return;
+            __asm__ volatile("" ::"v"(value));
+            constexpr int kRow = NMAX * 2 * sizeof(Real);
+            const int at = 128 * threadIdx.x;
+            if (at < nodes * kRow)
+                value = *reinterpret_cast<const uint32_t *>((const char *)(const Real *)a.ew +
+                                                            (size_t)next * kQ * kRow + at);
+        }
+    }
+};
+
 // The block's LDS state, [slot][thread]: one allocation per kernel that uses
 // it, NMAX slots (the batched kernel, whose structures differ in N).
 template <typename Real, int NMAX>
@@ -467,7 +493,9 @@ __device__ __forceinline__ void simulate_lds(const PathArgs<Real> &a, int64_t gi
         if (j >= a.off) xs[j * kBlock] = Real(0);
     int m = 0, js = 0;
     const int K = a.N * a.s;
+    TableTouch<Real, NMAX, SCHEME> touch;
     for (int k = 0; k < K; ++k) {
+        touch.step(a, k, K);
         const cptr<double> sc = a.steps + 4 * m;
         const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
         const uint4 w = philox4x32_10(
@@ -518,7 +546,9 @@ __device__ __forceinline__ void simulate(const PathArgs<Real> &a, int64_t gid) {
     for (int j = 0; j < NMAX; ++j) X[j] = Real(0);
     int m = 0, js = 0;
     const int K = a.N * a.s;
+    TableTouch<Real, NMAX, SCHEME> touch;
     for (int k = 0; k < K; ++k) {
+        touch.step(a, k, K);
         const cptr<double> sc = a.steps + 4 * m;
         const StepConsts cst{sc[0], sc[1], sc[2], sc[3]};
         const uint4 w = philox4x32_10(
