@@ -284,54 +284,11 @@ constexpr int kAnyProduct = -1;
 // value sum_{l>=c} delta_l (L_l - K) Q_l with Q_l = prod_{j>l}(1 + delta_j L_j);
 // its floating leg telescopes, sum_{l>=c} delta_l L_l Q_l = M - 1, and its
 // fixed leg is K A with A = sum_{l>=c} delta_l Q_l.
-template <typename Real, int NMAX, int J0>
-__device__ __forceinline__ void caplet_payoff(const PathArgs<Real> &a, int m, int64_t gid,
-                                              bool active, const Real (&X)[NMAX]) {
-    const int r = m;  // caplet on the rate with maturity T_{m+1}
-    double D = 1.0;
-#pragma unroll
-    for (int j = J0 + 1; j < NMAX; ++j)
-        D *= 1.0 + a.deltas[j] * a.L0s[j] * static_cast<double>(exp(X[j]));
-    const double Lc = a.L0s[J0] * static_cast<double>(exp(X[J0]));
-    if (a.path_fix != nullptr && active) {
-        a.path_fix[gid * 2 * a.N + 2 * r] = Lc;
-        a.path_fix[gid * 2 * a.N + 2 * r + 1] = D;
-    }
-    const int S = a.S;
-    const int nstat = 3 * S + 2;
-    const int64_t wave = gid / kWave;
-    double *out = a.partials + ((size_t)wave * a.N + r) * nstat;
-    const bool lane0 = (threadIdx.x % kWave) == 0;
-    for (int t = 0; t < S; ++t) {
-        const double K = a.strikes[r * S + t];
-        const double pay = active ? D * fmax(Lc - K, 0.0) : 0.0;
-        const double s1 = wave_sum(pay);
-        const double s2 = wave_sum(pay * pay);
-        const double ni = wave_sum((active && Lc > K) ? 1.0 : 0.0);
-        if (lane0) {
-            out[t] = s1;
-            out[S + t] = s2;
-            out[2 * S + t] = ni;
-        }
-    }
-    const double M = active ? D * (1.0 + a.deltas[J0] * Lc) : 0.0;
-    const double m1 = wave_sum(M);
-    const double m2 = wave_sum(M * M);
-    if (lane0) {
-        out[3 * S] = m1;
-        out[3 * S + 1] = m2;
-    }
-}
-
 template <typename Real, int NMAX, int J0, int PRODUCT>
 __device__ __forceinline__ void payoff(const PathArgs<Real> &a, int m, int64_t gid, bool active,
                                        const Real (&X)[NMAX]) {
-    if constexpr (PRODUCT == LLL_CAPLETS) {
-        caplet_payoff<Real, NMAX, J0>(a, m, gid, active, X);
-        return;
-    }
-    // Same arithmetic as payoff_lds (so the kernels that read the product at
-    // run time reproduce the LDS kernels bit for bit): one pass from the last
+    // Same arithmetic as payoff_lds (so that all kernels' sums are the same
+    // bit for bit): one pass from the last
     // rate down, Q = prod_{j>l}(1 + delta_j L_j) before slot l is multiplied
     // in; D = Q at slot J0, M = Q at the end.
     const int r = m;  // the rate with maturity T_{m+1}

@@ -73,3 +73,17 @@ def test_prices_of_a_split_range(gpu_lib, scheme, N, s, fp64, kw):
     assert np.allclose(price, ref["price"], rtol=1e-12, atol=0)
     assert np.array_equal(itm, ref["n_itm"])
     assert np.allclose(resid, ref["mart_resid"], rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("scheme", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("N,s,kw", [(6, 3, {}), (13, 2, dict(S=4)), (19, 2, dict(S=2)),
+                                    (24, 2, dict(product=1)), (40, 2, dict(S=3)),
+                                    (11, 2, dict(product=1, S=3))])
+def test_partial_sums_equal_the_wide_kernels(gpu_lib, scheme, N, s, kw):
+    """The sums of 64 paths do not depend on the kernel (FP32): shards of a run concatenate."""
+    ts = _structure(N, s, **kw)
+    with gpu_lib.Plan(ts, precision=0, max_paths=WIDE) as plan:
+        plan.execute(scheme, WIDE, seed=11)
+        wide = plan.partials()[:3]
+        plan.execute(scheme, 192, seed=11)
+        assert np.array_equal(plan.partials(), wide)
