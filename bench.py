@@ -209,7 +209,7 @@ def bench_adjoint(lll, stream, n: int = 1 << 20) -> dict:
     ts = workloads.adjoint_greeks()
     with lll.Plan(ts, precision=lll.FP32, max_paths=n) as plan:
         plan.set_timing(True)
-        plan.greeks(n, seed=1, stream=stream)   # warmup (allocates checkpoints)
+        plan.greeks(n, seed=1, stream=stream)   # warmup (allocates the states)
         plan.greeks(n, seed=1, stream=stream)
         ms = plan.timing()["paths"]
         g = plan.greeks_results(stream)

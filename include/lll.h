@@ -17,14 +17,14 @@
  *               quadrature); error O(|L|^2);
  *   LLL_SECOND_ORDER the same expansion to second order (eq. (drifta2), its
  *               first-order bracket with the signs of eq. (drifta)); the
- *               truncated product is integrated with the 64-node rule;
+ *               truncated product is integrated with LLL_FULL's rules;
  *               error O(|L|^3);
  *   LLL_PICARD_MP    LLL_PICARD computed in a maturity-parallel layout: under
  *               the Picard approximation the drift of every step depends on
  *               the predictor path only (Section 3), so the drift integrals
  *               of all accrual periods are computed at once, spread over
- *               (group of 4 paths, period, quadrature node) instead of one
- *               path per lane.  The same estimator as LLL_PICARD (equal up to
+ *               (64 paths, period, window of steps) instead of one path per
+ *               lane through all steps.  The same estimator as LLL_PICARD (equal up to
  *               FP32 summation order) for runs with few paths and many rates;
  *               FP32 plans, NIG driver, N up to LLL_N_MAX_MP;
  *   LLL_EXACT   the LLL_FULL estimator with the drift taken from the exact
@@ -42,7 +42,8 @@
  *
  * driven by a normal inverse Gaussian Lévy process (Section 4) or, as a
  * special case, by a Brownian motion.  The jump integral of the drift is the
- * closed-form cumulant plus a 64-node quadrature of the coupling term.
+ * closed-form cumulant plus a quadrature of the coupling term (64 nodes, reduced
+ * to a Gauss rule of as few as the precision allows per period: lll_plan_nodes).
  *
  * Conventions
  *   - Rates are 0-indexed: entry r is the paper's rate i = r + 1 with
@@ -161,10 +162,10 @@ int lll_plan_create(const lll_term_structure *ts, int precision, int64_t max_pat
  * allocated on its first use, LLL_ENOMEM if that fails); the path kernel over
  * paths path_offset .. path_offset + n_paths - 1; the deterministic FP64
  * reduction of the payoff sums.  Asynchronous: results are read with
- * lll_plan_results.  LLL_PICARD_MP replaces the path kernel by three kernels
- * (predictor and increments, per-period drift integrals, payoffs) over chunks
- * of paths whose buffers (ell at the predictor for every step, rate and path:
- * 4 K N bytes per path, plus 4 N^2) stay within 2 GiB; they are allocated on
+ * lll_plan_results.  LLL_PICARD_MP replaces the path kernel by kernels for
+ * the increments, the predictor, the drift integrals of windows of steps and the
+ * payoffs over chunks of paths whose buffers (increments, predictor and state
+ * moves of every window and rate) stay within 2 GiB; they are allocated on
  * its first use (LLL_ENOMEM if that fails); LLL_EUNSUPPORTED on FP64 plans or
  * the Brownian driver.  Plans with N > LLL_N_MAX run only LLL_PICARD_MP
  * (LLL_EUNSUPPORTED for the other schemes).  If path_fix_dev is not NULL it receives, for every path
@@ -272,11 +273,12 @@ int lll_price_caplets_static(const lll_term_structure *ts, int64_t n_paths, int 
  * of every product price (strike 0; caplets or the co-terminal swaptions of
  * the plan's product) with respect to the initial forwards L(0, T_l) and to a parallel
  * shift of each rate's volatility curve lambda(., T_l) (all steps k).  The
- * forward pass checkpoints the live rates at every tenor date; each product's
- * reverse sweep recomputes one accrual period at a time from its checkpoint.
- * B(0, T_1) is held fixed, so dP/dL0 includes the dependence of B(0, T_*) on
- * the forwards (paper Section 3.3, eq. (caplet)).  Checkpoint and scratch
- * buffers (about (N (N+1) / 2 + N + s nmax + s) x 4 bytes per path) are
+ * forward pass keeps the live rates of every step; each product's reverse sweep
+ * walks back from its fixing over them, on the caller's and three side streams
+ * joined to it.  B(0, T_1) is held fixed, so dP/dL0 includes the dependence of
+ * B(0, T_*) on the forwards (paper Section 3.3, eq. (caplet)).  The states (about
+ * (s N (N+1) / 2 + K + 2 N) x 4 bytes per path) go in chunks of paths within 16 GiB,
+ * smaller ones where memory is short; they are
  * allocated on the first call and kept by the plan.  LLL_EUNSUPPORTED for
  * N > LLL_N_MAX.  Asynchronous. */
 int lll_plan_greeks(lll_plan *plan, int64_t n_paths, uint64_t seed, void *stream);
@@ -287,10 +289,9 @@ int lll_plan_greeks(lll_plan *plan, int64_t n_paths, uint64_t seed, void *stream
  * reverse-mode differentiation of a scalar function of the prices needs.  One
  * reverse sweep, from the last fixing date to t = 0, whose state adjoint is
  * seeded with g_i times the payoff adjoint of product i at its fixing date
- * (paper Section 3.3, eq. (caplet); the swaption payoff of lll_product); per accrual period one kernel recomputes
- * the period from its tenor-date checkpoint and walks it back.  Cost: the
- * forward pass plus one recompute and one reverse pass, against one sweep per
- * product for the full Jacobian of lll_plan_greeks (same conventions, buffers
+ * (paper Section 3.3, eq. (caplet); the swaption payoff of lll_product); per accrual period one kernel walks
+ * back over the kept states.  Cost: the forward pass plus one reverse pass,
+ * against one sweep per product for the full Jacobian of lll_plan_greeks (same conventions, buffers
  * and restrictions; equal to g^T J up to FP32 summation order).
  * LLL_EINVAL for NULL or non-finite weights.  Asynchronous. */
 int lll_plan_greeks_vjp(lll_plan *plan, int64_t n_paths, uint64_t seed, const double *weights_host,

@@ -847,7 +847,7 @@ static int greeks_prepare(lll_plan *plan, int64_t n_paths) {
     if (e != hipSuccess) {
         lll::greeks_free(*plan);
         return fail(e == hipErrorOutOfMemory ? LLL_ENOMEM : LLL_EHIP,
-                    "allocating adjoint checkpoints: %s", hipGetErrorString(e));
+                    "allocating adjoint states: %s", hipGetErrorString(e));
     }
     return LLL_OK;
 }
