@@ -33,8 +33,11 @@
 // (gradient kernels 10.2 -> 8.1 ms at 2^18 paths),
 // then Xbar_l += ellbar_l ell_l (1 - ell_l), L0bar_l += ellbar_l ell_l (1 - ell_l) / L(0, T_l),
 // lambdabar_l += Xbar_l (dH - kappa'(lambda_l) dt).  L0bar_l L(0, T_l) collects the
-// same terms as Xbar_l, from the payoff's adjoint down to step 0, so it is Xbar_l
-// at the start: its wavefront sum is scaled by 1 / L(0, T_l) once.
+// same terms as Xbar_l, from the payoff's adjoint down to step 0, and its wavefront sum
+// is scaled by 1 / L(0, T_l) once.  It has an accumulator of its own: a step moves Xbar
+// by about dt times the drift's derivative, which the rounding of Xbar itself swallows when
+// the steps are many (taken from Xbar at the start, vector-Jacobian products were 1e-5
+// off FP64 at 400 steps a period; 1e-8 to 2e-8 with the accumulators).
 // The products are carried less one because a node of a period's rule can lie next to the
 // origin and hold most of the coupling: P - 1 formed from P is then P's FP32 rounding, and
 // the vol adjoints of 12 rates were 2e-3 to 3e-3 of their norm off FP64 with a node within
@@ -201,23 +204,24 @@ __device__ __forceinline__ void load_before(const PathArgs<float> &a, int m, int
     else load_state<NMAX, JC>(a, m - 1, a.s - 1, d, X);
 }
 
-// A reverse step holds X (loaded ahead), ell, Xb, R, lb, vb, a temporary and the vol
-// accumulators per rate: 8 registers, two wavefronts per SIMD up to 30 rates.
-// Beyond, the accumulators stay in LDS; beyond 34 rates, X is loaded after the node
-// loop instead of ahead of it.
+// A reverse step holds X (loaded ahead), ell, Xb, R, lb, vb, a temporary and the two
+// accumulators per rate: 9 registers, two wavefronts per SIMD up to 26 rates.  Beyond,
+// the accumulators stay in LDS; beyond 34 rates, X is loaded after the node loop instead of
+// ahead of it.
 template <int NMAX, int JC>
-constexpr bool kAccInLds = NMAX - JC > 30;
+constexpr bool kAccInLds = NMAX - JC > 26;
 template <int NMAX, int JC>
 constexpr bool kLoadAhead = NMAX - JC <= 34;
 
 // Reverse of step js of period m for the slots JC .. NMAX-1, given the state X
 // at the start of the step and Xb = adjoint of the state at its end (updated in
 // place to the adjoint at the start); X is then loaded with the state of the step
-// before.  The vol adjoints go to the LDS accumulators.
+// before.  The adjoints of L0 (times L0) and of the vol go to the lane's accumulators
+// acc[2 i] and acc[2 i + 1] of slot JC + i, in rows of kAdjBlock.
 template <int NMAX, int JC>
 __device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const AdjArgs &g, int m,
                                              int js, const float *d, float (&X)[NMAX],
-                                             float (&Xb)[NMAX], float *__restrict__ accV) {
+                                             float (&Xb)[NMAX], float *__restrict__ acc) {
     // Cbar = -dt Xbar: the factor -dt is applied to lb after the node loop and to
     // the node x in the vol adjoints
     const int k = m * a.s + js;
@@ -256,8 +260,10 @@ __device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const Adj
     }
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) {
-        accV[(j - JC) * kAdjBlock] += fmaf(Xb[j], dH - dk[j], vb[j]);
-        Xb[j] += lb[j] * mdt * ell[j] * (1.0f - ell[j]);
+        acc[(2 * (j - JC) + 1) * kAdjBlock] += fmaf(Xb[j], dH - dk[j], vb[j]);
+        const float move = lb[j] * mdt * ell[j] * (1.0f - ell[j]);
+        acc[2 * (j - JC) * kAdjBlock] += move;
+        Xb[j] += move;
     }
     if (!kLoadAhead<NMAX, JC> && k > 0) {
         __asm__ volatile("" ::: "memory");
@@ -265,9 +271,8 @@ __device__ __forceinline__ void reverse_step(const PathArgs<float> &a, const Adj
     }
 }
 
-// Adds w times the payoff adjoint of product c (strike 0; slot JC = off + c)
-// at its fixing date T_{c+1} to the state adjoint Xb, and loads the fixing state
-// into X.
+// Xb = w times the payoff adjoint of product c (strike 0; slot JC = off + c)
+// at its fixing date T_{c+1}, and X = the fixing state.
 //   caplet:   f = D (L_c - K)^+, D = prod_{l>c}(1 + delta_l L_l);
 //   swaption: f = (Q - 1 - K A)^+, Q = prod_{l>=c} b_l, b_l = 1 + delta_l L_l,
 //             A = sum_{l>=c} delta_l prod_{j>l} b_j, so that with
@@ -300,7 +305,7 @@ __device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const floa
         for (int j = JC; j < NMAX; ++j) {
             const double L = a.L0s[j] * static_cast<double>(expf(X[j]));
             const double b = 1.0 + a.deltas[j] * L;
-            Xb[j] += itm ? w * static_cast<float>(a.deltas[j] * L / b * (Q - K * S)) : 0.0f;
+            Xb[j] = itm ? w * static_cast<float>(a.deltas[j] * L / b * (Q - K * S)) : 0.0f;
             pre *= b;
             S = fma(a.deltas[j], Q / pre, S);
             __builtin_amdgcn_sched_barrier(0);
@@ -322,25 +327,33 @@ __device__ __forceinline__ void seed_caplet(const PathArgs<float> &a, const floa
     const float dXc = itm ? w * static_cast<float>(D * Lc) : 0.0f;
     const float dD = itm ? w * static_cast<float>(Lc - K) : 0.0f;
     const float Df = static_cast<float>(D);
-    Xb[JC] += dXc;
+    Xb[JC] = dXc;
 #pragma unroll
-    for (int j = JC + 1; j < NMAX; ++j) Xb[j] += dD * Df * ellf[j];
+    for (int j = JC + 1; j < NMAX; ++j) Xb[j] = dD * Df * ellf[j];
+}
+
+// The accumulators of a sweep or period: the L0 adjoints start at the payoff's.
+template <int NMAX, int JC>
+__device__ __forceinline__ void start_sums(const float (&Xb)[NMAX], float *__restrict__ acc) {
+#pragma unroll
+    for (int j = JC; j < NMAX; ++j) {
+        acc[2 * (j - JC) * kAdjBlock] = Xb[j];
+        acc[(2 * (j - JC) + 1) * kAdjBlock] = 0.0f;
+    }
 }
 
 // Sweep of the caplet fixing in slot JC (rate c = JC - off, period c).
 template <int NMAX, int JC>
 __device__ __forceinline__ void sweep(const PathArgs<float> &a, const AdjArgs &g, int64_t gid,
-                                      bool active, float *__restrict__ accV) {
+                                      bool active, float *__restrict__ acc) {
     const int lane = threadIdx.x;
     const int c = JC - a.off;
     const int N = a.N;
     const float *d = lane_rows(g, gid);
-#pragma unroll
-    for (int j = JC; j < NMAX; ++j) accV[(j - JC) * kAdjBlock + lane] = 0.0f;
+    acc += lane;
     float X[NMAX], Xb[NMAX];
-#pragma unroll
-    for (int j = 0; j < NMAX; ++j) Xb[j] = 0.0f;
     seed_caplet<NMAX, JC>(a, d, active, 1.0f, X, Xb);
+    start_sums<NMAX, JC>(Xb, acc);
     // skip the sweep when no lane of the wavefront has a nonzero adjoint
     bool any = false;
 #pragma unroll
@@ -349,15 +362,16 @@ __device__ __forceinline__ void sweep(const PathArgs<float> &a, const AdjArgs &g
         load_state<NMAX, JC>(a, c, a.s - 1, d, X);
         for (int m = c; m >= 0; --m)
             for (int js = a.s - 1; js >= 0; --js)
-                reverse_step<NMAX, JC>(a, g, m, js, d, X, Xb, accV + lane);
+                reverse_step<NMAX, JC>(a, g, m, js, d, X, Xb, acc);
     }
-    // wavefront sums of this caplet's adjoints (lanes past the end: Xb = 0)
+    // wavefront sums of this caplet's adjoints
     const int64_t wave = gid / kWave;
     double *out = g.gpart + (static_cast<int64_t>(wave) * N + c) * 2 * N;
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) {
-        const double l0 = detail::wave_sum(Xb[j]) * g.inv_L0[j];
-        const double vv = detail::wave_sum(active ? accV[(j - JC) * kAdjBlock + lane] : 0.0f);
+        const double l0 =
+            detail::wave_sum(active ? acc[2 * (j - JC) * kAdjBlock] : 0.0f) * g.inv_L0[j];
+        const double vv = detail::wave_sum(active ? acc[(2 * (j - JC) + 1) * kAdjBlock] : 0.0f);
         if (lane == 0) {
             out[j - a.off] = l0;
             out[N + j - a.off] = vv;
@@ -375,9 +389,8 @@ __device__ __forceinline__ void sweep(const PathArgs<float> &a, const AdjArgs &g
 // it takes the state adjoint carried from period m+1 (xb, by rate), adds the
 // seed of caplet m (weight w_m = g_m delta_m) at its fixing, reverses the
 // period and stores the adjoint at the period's start; the wavefront sums of
-// its vol adjoints are added to the per-wave partials (periods in launch order,
-// so the sums are deterministic), and the kernel of period 0 writes those of the
-// adjoint at the start.
+// the period's L0 and vol adjoints are added to the per-wave partials (periods in
+// launch order, so the sums are deterministic).
 struct VjpArgs {
     double *part;   // [waves][2N] sums of L0bar (first N) and vbar
     detail::cptr<float> w;  // [N] seeds g_m s_m of the products (device memory)
@@ -386,28 +399,28 @@ struct VjpArgs {
 template <int NMAX, int JC>
 __device__ __forceinline__ void vjp_period(const PathArgs<float> &a, const AdjArgs &g,
                                            const VjpArgs &v, int64_t gid, bool active,
-                                           float *__restrict__ accV) {
+                                           float *__restrict__ acc) {
     const int lane = threadIdx.x;
     const int m = JC - a.off;
     const float w = v.w[m];
     const int N = a.N;
     float *d = lane_rows(g, gid);
     float *xb = d + at_xb(a, m);
-#pragma unroll
-    for (int j = JC; j < NMAX; ++j) accV[(j - JC) * kAdjBlock + lane] = 0.0f;
+    acc += lane;
     float X[NMAX], Xb[NMAX];
-    Xb[JC] = 0.0f;
-    // rate m is fixed after period m: only the later rates carry an adjoint
-#pragma unroll
-    for (int j = JC + 1; j < NMAX; ++j)
-        Xb[j] = m < N - 1 ? xb[(j - JC) * kWave] : 0.0f;
     seed_caplet<NMAX, JC>(a, d, active, w, X, Xb);
+    start_sums<NMAX, JC>(Xb, acc);
+    // rate m is fixed after period m: only the later rates carry an adjoint
+    if (m < N - 1) {
+#pragma unroll
+        for (int j = JC + 1; j < NMAX; ++j) Xb[j] += xb[(j - JC) * kWave];
+    }
     bool any = false;
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) any = any || (Xb[j] != 0.0f);
     if (__any(any)) {
         load_state<NMAX, JC>(a, m, a.s - 1, d, X);
-        for (int js = a.s - 1; js >= 0; --js) reverse_step<NMAX, JC>(a, g, m, js, d, X, Xb, accV + lane);
+        for (int js = a.s - 1; js >= 0; --js) reverse_step<NMAX, JC>(a, g, m, js, d, X, Xb, acc);
     }
     if (m > 0) {
 #pragma unroll
@@ -416,14 +429,12 @@ __device__ __forceinline__ void vjp_period(const PathArgs<float> &a, const AdjAr
     double *out = v.part + (gid / kWave) * 2 * N;
 #pragma unroll
     for (int j = JC; j < NMAX; ++j) {
-        const double vv = detail::wave_sum(active ? accV[(j - JC) * kAdjBlock + lane] : 0.0f);
-        if (lane == 0) out[N + j - a.off] += vv;
-    }
-    if (m == 0) {
-#pragma unroll
-        for (int j = JC; j < NMAX; ++j) {
-            const double l0 = detail::wave_sum(Xb[j]) * g.inv_L0[j];
-            if (lane == 0) out[j - a.off] = l0;
+        const double l0 =
+            detail::wave_sum(active ? acc[2 * (j - JC) * kAdjBlock] : 0.0f) * g.inv_L0[j];
+        const double vv = detail::wave_sum(active ? acc[(2 * (j - JC) + 1) * kAdjBlock] : 0.0f);
+        if (lane == 0) {
+            out[j - a.off] += l0;
+            out[N + j - a.off] += vv;
         }
     }
 }
@@ -434,21 +445,21 @@ template <int NMAX, int JC>
 __global__ void __launch_bounds__(kAdjBlock, (kAccInLds<NMAX, JC> ? 2 : 1)) sweep_kernel(PathArgs<float> a, AdjArgs g) {
     // per-lane accumulators of the carried slots JC..NMAX-1 only (LDS bounds
     // the resident wavefronts of the long sweeps)
-    __shared__ float accV[(NMAX - JC) * kAdjBlock];
+    __shared__ float acc[2 * (NMAX - JC) * kAdjBlock];
     const int64_t gid = static_cast<int64_t>(blockIdx.x) * kAdjBlock + threadIdx.x;
     const int64_t wave_first = gid - threadIdx.x;
     if (wave_first >= a.n_paths) return;
-    sweep<NMAX, JC>(a, g, gid, gid < a.n_paths, accV);
+    sweep<NMAX, JC>(a, g, gid, gid < a.n_paths, acc);
 }
 
 template <int NMAX, int JC>
 __global__ void __launch_bounds__(kAdjBlock, (kAccInLds<NMAX, JC> ? 2 : 1))
     vjp_period_kernel(PathArgs<float> a, AdjArgs g, VjpArgs v) {
-    __shared__ float accV[(NMAX - JC) * kAdjBlock];
+    __shared__ float acc[2 * (NMAX - JC) * kAdjBlock];
     const int64_t gid = static_cast<int64_t>(blockIdx.x) * kAdjBlock + threadIdx.x;
     const int64_t wave_first = gid - threadIdx.x;
     if (wave_first >= a.n_paths) return;
-    vjp_period<NMAX, JC>(a, g, v, gid, gid < a.n_paths, accV);
+    vjp_period<NMAX, JC>(a, g, v, gid, gid < a.n_paths, acc);
 }
 
 template <int NMAX, int PRODUCT>

@@ -9,7 +9,11 @@ node of one period is within the stated distance.
 
 The reference differentiates the Euler recursion on the 64-node rule in FP64 by torch's
 reverse mode.  Bar 1e-5 of the norm: the FP32 recursion rounds each of the 36 steps at 2^-24 of
-terms of one sign (36 * 2^-24 = 2e-6), in the states and in the sweep."""
+terms of one sign (36 * 2^-24 = 2e-6), in the states and in the sweep.
+
+With hundreds of steps a period, a step moves the state adjoint by less than its rounding; the
+forward derivatives have sums of their own and stay within 1e-6 of the norm (the payoff's
+adjoint and the sum of the moves, each rounded at 2^-24, with a factor of 16 to spare)."""
 import numpy as np
 import pytest
 import torch
@@ -26,6 +30,11 @@ def structure(beta, product):
     ts = workloads.make_structure(N, 0.25, 0.03 + 0.001 * np.arange(N), S_STEPS,
                                   workloads.exp_decay_vol(), [0.8], beta=beta)
     return workloads.coterminal_swaptions(ts, [0.8]) if product else ts
+
+
+def long_structure(n, s):
+    return workloads.make_structure(n, 0.25, 0.03 + 0.001 * np.arange(n), s,
+                                    workloads.exp_decay_vol(), [0.8])
 
 
 def middle_node(lib, beta, m):
@@ -54,8 +63,9 @@ def beta_with_node_at_origin(lib, distance):
     raise AssertionError("no period's middle node crosses the origin")
 
 
-def fp64_jacobian(plan, ts):
+def fp64_jacobian(plan, ts, paths=PATHS):
     """Prices (strike 0) and their derivatives, all in FP64 on the host."""
+    N, s = ts.n_rates, ts.steps_per_period
     t = plan.tables()
     x, w = torch.tensor(t["x"]), torch.tensor(t["w"])
     L0 = torch.tensor(ts.L0, requires_grad=True)
@@ -63,14 +73,14 @@ def fp64_jacobian(plan, ts):
     dl = torch.tensor(ts.delta)
     a, b, dn = ts.alpha, ts.beta, ts.delta_nig
     gamma = np.sqrt(a * a - b * b)
-    X = [torch.zeros(PATHS, dtype=torch.float64) for _ in range(N)]
+    X = [torch.zeros(paths, dtype=torch.float64) for _ in range(N)]
     price = []
     B0T = ts.B0_T1 / torch.prod(1.0 + dl * L0)
-    for k in range(N * S_STEPS):
-        m = k // S_STEPS
-        dt = (ts.tenor[m] - (ts.tenor[m - 1] if m else 0.0)) / S_STEPS
-        dH = torch.tensor(plan.increments(k, 0, PATHS, seed=SEED)[1])
-        R = torch.zeros(PATHS, len(x), dtype=torch.float64)
+    for k in range(N * s):
+        m = k // s
+        dt = (ts.tenor[m] - (ts.tenor[m - 1] if m else 0.0)) / s
+        dH = torch.tensor(plan.increments(k, 0, paths, seed=SEED)[1])
+        R = torch.zeros(paths, len(x), dtype=torch.float64)
         for i in range(N - 1, m - 1, -1):
             lam = ts.vol[k, i] + v[i]
             E = torch.expm1(lam * x)
@@ -80,9 +90,9 @@ def fp64_jacobian(plan, ts):
             C = (R * (w * E)).sum(1)
             R = R + ell * E * (1.0 + R)
             X[i] = X[i] + (-kappa - C) * dt + lam * dH
-        if (k + 1) % S_STEPS == 0:
+        if (k + 1) % s == 0:
             L = [L0[l] * torch.exp(X[l]) for l in range(m, N)]
-            Q, A = torch.ones(PATHS, dtype=torch.float64), 0.0
+            Q, A = torch.ones(paths, dtype=torch.float64), 0.0
             for l in range(N - 1, m - 1, -1):
                 D = Q
                 A = A + dl[l] * Q
@@ -115,3 +125,18 @@ def test_derivatives_with_a_node_next_to_the_origin(gpu_lib, distance, product):
                                   ("vjp_vol", vjp["vjp_vol"], g @ dV))}
     print(f"beta {beta:.9f}", {k: f"{e:.1e}" for k, e in err.items()}, flush=True)
     assert max(err.values()) <= BAR, err
+
+
+@pytest.mark.parametrize("n,s", [(4, 100), (4, 400), (10, 50)])
+def test_forward_derivatives_over_many_steps(gpu_lib, n, s):
+    ts, paths = long_structure(n, s), 64
+    with gpu_lib.Plan(ts, max_paths=paths) as plan:
+        ref, _ = fp64_jacobian(plan, ts, paths)
+        plan.greeks(paths, seed=SEED)
+        err = [np.linalg.norm(plan.greeks_results()["dP_dL0"] - ref) / np.linalg.norm(ref)]
+        for g in (np.ones(n), np.linspace(-0.5, 1.5, n)):
+            plan.greeks_vjp(paths, g, seed=SEED)
+            got = plan.greeks_vjp_results()["vjp_L0"]
+            err.append(np.linalg.norm(got - g @ ref) / np.linalg.norm(g @ ref))
+    print(n, s, [f"{e:.1e}" for e in err], flush=True)
+    assert max(err) <= 1e-6, err
