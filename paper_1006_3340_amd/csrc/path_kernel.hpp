@@ -536,7 +536,7 @@ __global__ void __launch_bounds__(kBlock) path_kernel(PathArgs<Real> a) {
 // Drift of the live rates at step k for given rate vectors (inspection): the
 // same coupling code as the path kernel, one state per lane.
 template <typename Real, int NMAX, int J0>
-__device__ void drift_one(const PathArgs<Real> &a, int k, const double *__restrict__ L,
+__device__ __forceinline__ void drift_one(const PathArgs<Real> &a, int k, const double *__restrict__ L,
                           const double *__restrict__ kappa, double *__restrict__ b) {
     Real ell[NMAX], C[NMAX];
 #pragma unroll
@@ -556,8 +556,12 @@ __device__ void drift_one(const PathArgs<Real> &a, int k, const double *__restri
     }
 }
 
+// Inlined into the kernel, as everything here: left to itself the compiler makes one
+// function of the wide buckets' bodies, so large that branches across it need a register
+// pair for their target, and takes the pair that holds the function's return address.  With 32
+// and 40 slots the kernel then never came back.
 template <typename Real, int NMAX, int... Js>
-__device__ void dispatch_drift(std::integer_sequence<int, Js...>, int j0, const PathArgs<Real> &a,
+__device__ __forceinline__ void dispatch_drift(std::integer_sequence<int, Js...>, int j0, const PathArgs<Real> &a,
                                int k, const double *L, const double *kappa, double *b) {
     (void)((j0 == Js ? (drift_one<Real, NMAX, Js>(a, k, L, kappa, b), 0) : 0) + ...);
 }
