@@ -43,7 +43,7 @@ MLP_SOURCES = ["paper_1006_3340_amd/csrc/mlp_path.hip", "paper_1006_3340_amd/csr
 # rocprofv3 --pmc figures of the surrogate pricing kernel at 2^20 paths
 # (profiles/mlp_kernels_mlp_n40_mfma_counters.md), by source hash: a changed
 # kernel reports none
-MLP_COUNTERS = {"7ad88a189d8670f9": {
+MLP_COUNTERS = {"273149fff983bf5a": {
     "source": "profiles/mlp_kernels_mlp_n40_mfma_counters.md",
     "mlp_path_kernel_ms": 529.24, "clock_ghz": 2.38,
     "counted_mfma_flop": 2.178e+14, "counted_mfma_tflops": 411.4,

@@ -143,7 +143,7 @@ namespace {
 using lll::validate;
 
 void free_tables(lll::DeviceTables &d) {
-    void *ptrs[] = {d.arena, d.E, d.vol_base, d.k2, d.kex, d.xex};
+    void *ptrs[] = {d.arena, d.vol_base, d.k2, d.kex, d.xex};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     d = lll::DeviceTables{};
@@ -607,14 +607,13 @@ int lll_plan_tables(lll_plan *plan, double *x_host, double *w_host, double *kapp
     if (!plan) return fail(LLL_EINVAL, "plan is NULL");
     hipStream_t st = as_stream(stream);
     const size_t K = plan->K, N = plan->N, Q = lll::kQSize;
-    // the 64-node tables are made only for a plan that holds E: for this call
-    const bool held = plan->d.E != nullptr;
-    hipError_t e = held ? hipSuccess : hipMalloc(&plan->d.E, K * N * Q * sizeof(double) + 16);
-    if (e != hipSuccess) {
-        plan->d.E = nullptr;
-        return fail(LLL_ENOMEM, "table E: %s", hipGetErrorString(e));
-    }
+    // the 64-node table is made for this call, in a buffer of its own (a pass on another
+    // thread does not see it)
+    double *E = nullptr;
+    hipError_t e = hipMalloc(&E, K * N * Q * sizeof(double) + 16);
+    if (e != hipSuccess) return fail(LLL_ENOMEM, "table E: %s", hipGetErrorString(e));
     e = lll::launch_precompute(*plan, st);
+    if (e == hipSuccess) e = lll::launch_full_tables(*plan, E, st);
     auto D2H = [&](double *dst, const double *src, size_t n) {
         if (dst && e == hipSuccess)
             e = hipMemcpyAsync(dst, src, n * sizeof(double), hipMemcpyDeviceToHost, st);
@@ -622,13 +621,10 @@ int lll_plan_tables(lll_plan *plan, double *x_host, double *w_host, double *kapp
     D2H(x_host, plan->d.x, Q);
     D2H(w_host, plan->d.w, Q);
     D2H(kappa_host, plan->d.kappa, K * N);
-    D2H(E_host, plan->d.E, K * N * Q);
+    D2H(E_host, E, K * N * Q);
     D2H(b0_host, plan->d.b0, K * N);
     const hipError_t done = hipStreamSynchronize(st);
-    if (!held) {
-        (void)hipFree(plan->d.E);
-        plan->d.E = nullptr;
-    }
+    (void)hipFree(E);
     if (e == hipSuccess) e = done;
     if (e != hipSuccess) return hip_fail(e, "reading tables");
     return LLL_OK;

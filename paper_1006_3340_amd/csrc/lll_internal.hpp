@@ -23,14 +23,13 @@ int bucket_for(int n_rates, bool slots20);
 
 struct DeviceTables {
     void *arena = nullptr;     // the one allocation that holds the buffers below but
-                               // E, vol_base, k2, kex, xex (null: not the plan's own)
+                               // vol_base, k2, kex, xex (null: not the plan's own)
     // FP64 inputs (device)
     double *tenor = nullptr, *delta = nullptr, *L0 = nullptr, *vol = nullptr, *strikes = nullptr;
     // FP64 precompute, inspection layout
     double *x = nullptr, *w = nullptr;          // [Q]
     double *kappa = nullptr;                    // [K][N]
-    double *E = nullptr;                        // [K][N][Q], or null: made on demand
-    double *b0 = nullptr;                       // [K][N], written with E
+    double *b0 = nullptr;                       // [K][N], written with the 64-node table
     double *gx = nullptr, *gw = nullptr;        // [N][Q] the periods' Gauss nodes and weights
     int *nq = nullptr;                          // [K] node count of each step's period
     double *steps = nullptr;                    // [N][4] per-period increment constants
@@ -174,7 +173,9 @@ PassArgs pass_args(const lll_plan &p);  // paths.hip
 
 // precompute.hip
 hipError_t launch_precompute(const lll_plan &p, hipStream_t st);
-// the same for the FP32 structures of a device array, in one launch each kernel
+// after it: E [K][N][Q] at the 64 nodes, and the plan's b0 on them
+hipError_t launch_full_tables(const lll_plan &p, double *E, hipStream_t st);
+// the same as launch_precompute for the FP32 structures of a device array, in one launch each kernel
 hipError_t launch_precompute_batch(const PassArgs *many, int structures, int max_N, int max_K,
                                    hipStream_t st);
 // precompute.hip: replace the initial forwards (L0_dev [N], or NULL) and shift

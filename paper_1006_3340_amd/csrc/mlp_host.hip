@@ -15,7 +15,7 @@ namespace lll {
 namespace mlp {
 hipError_t launch_record(const lll_plan &p, int64_t n_paths, int R, uint64_t seed, float *states,
                          int *kidx, hipStream_t st);
-hipError_t launch_labels(const lll_plan &p, const float *states, const int *kidx,
+hipError_t launch_labels(const lll_plan &p, const double *E, const float *states, const int *kidx,
                          const int64_t *poff, int64_t n_states, __bf16 *feat, float *label,
                          hipStream_t st);
 hipError_t launch_stats(const lll_plan &p, const float *states, const int *kidx, int64_t n_states,
@@ -207,20 +207,21 @@ int lll_mlp_generate(lll_mlp *m, lll_plan *plan, int64_t n_paths, int records, u
         return fail(LLL_ENOMEM, "training data (%lld pairs): %s", (long long)acc,
                     hipGetErrorString(e));
     }
-    // the labels integrate on the 64 nodes: hold their table for this call
-    const bool held = plan->d.E != nullptr;
-    if (!held) e = hipMalloc(&plan->d.E, sizeof(double) * plan->K * plan->N * lll::kQSize);
+    // the labels integrate on the 64 nodes: their table is made for this call
+    double *E = nullptr;
+    e = hipMalloc(&E, sizeof(double) * plan->K * plan->N * lll::kQSize);
     if (e != hipSuccess) {
-        plan->d.E = nullptr;
         free_data(m);
         return fail(LLL_ENOMEM, "table E: %s", hipGetErrorString(e));
     }
     e = hipMemcpyAsync(m->poff_dev, m->poff.data(), sizeof(int64_t) * (m->n_states + 1),
                        hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = lll::launch_precompute(*plan, st);
+    if (e == hipSuccess) e = lll::launch_full_tables(*plan, E, st);
     if (e == hipSuccess) e = launch_record(*plan, n_paths, records, seed, m->states, m->kidx, st);
     if (e == hipSuccess)
-        e = launch_labels(*plan, m->states, m->kidx, m->poff_dev, m->n_states, m->feat, m->label, st);
+        e = launch_labels(*plan, E, m->states, m->kidx, m->poff_dev, m->n_states, m->feat, m->label,
+                          st);
     if (e == hipSuccess)
         e = launch_stats(*plan, m->states, m->kidx, m->n_states, m->label, m->n_pairs, m->info, st);
     if (e == hipSuccess)
@@ -228,10 +229,7 @@ int lll_mlp_generate(lll_mlp *m, lll_plan *plan, int64_t n_paths, int records, u
                            hipMemcpyDeviceToHost, st);
     const hipError_t done = hipStreamSynchronize(st);
     if (e == hipSuccess) e = done;
-    if (!held) {
-        (void)hipFree(plan->d.E);
-        plan->d.E = nullptr;
-    }
+    (void)hipFree(E);
     if (e != hipSuccess) {
         free_data(m);
         return hip_fail(e, "generating training pairs");

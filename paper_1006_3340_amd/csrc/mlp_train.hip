@@ -564,12 +564,12 @@ hipError_t launch_record(const lll_plan &p, int64_t n_paths, int R, uint64_t see
     return hipGetLastError();
 }
 
-hipError_t launch_labels(const lll_plan &p, const float *states, const int *kidx,
+hipError_t launch_labels(const lll_plan &p, const double *E, const float *states, const int *kidx,
                          const int64_t *poff, int64_t n_states, __bf16 *feat, float *label,
                          hipStream_t st) {
     const dim3 grid(static_cast<unsigned>((n_states + 63) / 64));
     hipLaunchKernelGGL(label_kernel, grid, dim3(64), 0, st, states, kidx, poff, n_states, p.nmax,
-                       p.off, p.N, p.s, p.d.tenor, p.d.delta, p.d.L0, p.d.vol, p.d.E, p.d.w,
+                       p.off, p.N, p.s, p.d.tenor, p.d.delta, p.d.L0, p.d.vol, E, p.d.w,
                        p.alpha, p.beta, p.delta_nig, feat, label);
     return hipGetLastError();
 }

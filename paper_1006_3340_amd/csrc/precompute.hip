@@ -490,8 +490,8 @@ __global__ void __launch_bounds__(256) setup_tables_kernel(PassArgs one,
 }
 
 // E at the 64 nodes and the frozen drift on them, [K][N][Q] and [K][N] FP64:
-// what lll_plan_tables shows and the training labels integrate on (made only
-// for plans that hold the table).  One block of 64 threads (node q) per step.
+// what lll_plan_tables shows and the training labels integrate on (made for those
+// calls only).  One block of 64 threads (node q) per step.
 __global__ void __launch_bounds__(64) full_tables_kernel(
     const double *__restrict__ delta, const double *__restrict__ L0,
     const double *__restrict__ vol, const double *__restrict__ x_in,
@@ -542,16 +542,6 @@ hipError_t launch_setup(const PassArgs &one, const PassArgs *many, int structure
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(setup_tables_kernel<Real>, dim3(max_K, structures), dim3(256), 0, st, one,
                        many);
-    return hipGetLastError();
-}
-
-template <typename Real>
-hipError_t launch_precompute_t(const lll_plan &p, hipStream_t st) {
-    const DeviceTables &d = p.d;
-    hipError_t e = launch_setup<Real>(pass_args(p), nullptr, 1, p.N, p.K, st);
-    if (e != hipSuccess || !d.E) return e;
-    hipLaunchKernelGGL(full_tables_kernel, dim3(p.K), dim3(64), 0, st, d.delta, d.L0, d.vol, d.x,
-                       d.w, d.kappa, p.N, p.s, p.driver, p.c, d.E, d.b0);
     return hipGetLastError();
 }
 
@@ -626,8 +616,16 @@ hipError_t launch_set_inputs(const lll_plan &p, const double *L0_dev, const doub
 }
 
 hipError_t launch_precompute(const lll_plan &p, hipStream_t st) {
-    return p.precision == LLL_FP64 ? launch_precompute_t<double>(p, st)
-                                   : launch_precompute_t<float>(p, st);
+    const PassArgs a = pass_args(p);
+    return p.precision == LLL_FP64 ? launch_setup<double>(a, nullptr, 1, p.N, p.K, st)
+                                   : launch_setup<float>(a, nullptr, 1, p.N, p.K, st);
+}
+
+hipError_t launch_full_tables(const lll_plan &p, double *E, hipStream_t st) {
+    const DeviceTables &d = p.d;
+    hipLaunchKernelGGL(full_tables_kernel, dim3(p.K), dim3(64), 0, st, d.delta, d.L0, d.vol, d.x,
+                       d.w, d.kappa, p.N, p.s, p.driver, p.c, E, d.b0);
+    return hipGetLastError();
 }
 
 hipError_t launch_precompute_batch(const PassArgs *many, int structures, int max_N, int max_K,

@@ -35,6 +35,7 @@ hipError_t measure_mfma_peak(hipStream_t, double *) { return hipErrorNotSupporte
 hipError_t launch_greeks_vjp(const lll_plan &, int64_t, uint64_t, const double *, const double *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_increments(const lll_plan &, int, int64_t, int64_t, uint64_t, double *, double *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_precompute(const lll_plan &, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_full_tables(const lll_plan &, double *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_set_inputs(const lll_plan &, const double *, const double *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_first_order_tables(const lll_plan &, hipStream_t) { return hipErrorNotSupported; }
 }  // namespace lll
