@@ -23,7 +23,11 @@ int fail(int code, const char *fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    g_last_error = buf;
+    try {
+        g_last_error = buf;
+    } catch (...) {  // no memory for the message: the status alone
+        g_last_error.clear();
+    }
     return code;
 }
 
@@ -635,17 +639,20 @@ int lll_plan_nodes(lll_plan *plan, int32_t *count_host, double *x_host, double *
     if (!plan) return fail(LLL_EINVAL, "plan is NULL");
     hipStream_t st = as_stream(stream);
     const size_t N = plan->N, K = plan->K, Q = lll::kQSize;
-    std::vector<int> nq(K);
+    int *nq = count_host ? new (std::nothrow) int[K] : nullptr;
+    if (count_host && !nq) return fail(LLL_ENOMEM, "host allocation failed");
     hipError_t e = lll::launch_precompute(*plan, st);
     auto D2H = [&](void *dst, const void *src, size_t bytes) {
         if (dst && e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
     };
-    D2H(nq.data(), plan->d.nq, K * sizeof(int));
+    D2H(nq, plan->d.nq, K * sizeof(int));
     D2H(x_host, plan->d.gx, N * Q * sizeof(double));
     D2H(w_host, plan->d.gw, N * Q * sizeof(double));
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const hipError_t done = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = done;
+    for (size_t m = 0; e == hipSuccess && count_host && m < N; ++m) count_host[m] = nq[m * plan->s];
+    delete[] nq;
     if (e != hipSuccess) return hip_fail(e, "reading nodes");
-    for (size_t m = 0; count_host && m < N; ++m) count_host[m] = nq[m * plan->s];
     return LLL_OK;
 }
 
