@@ -548,19 +548,10 @@ hipError_t launch_adjoint_bucket(const PathArgs<float> &a, const AdjArgs &g, con
                                  hipStream_t st) {
     const dim3 grid(static_cast<unsigned>((a.n_paths + kAdjBlock - 1) / kAdjBlock));
     hipError_t e = launch_forward<NMAX>(grid, a, g, st);
-    if (e == hipSuccess) e = hipEventRecord(ss.fork, st);
-    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i)
-        e = hipStreamWaitEvent(ss.side[i], ss.fork, 0);
-    for (int c = 0; c < a.N && e == hipSuccess; ++c) {
-        const int i = c % (kSideStreams + 1);
-        e = launch_sweep<NMAX>(std::make_integer_sequence<int, NMAX>{}, a.off + c, grid, a, g,
-                               i == 0 ? st : ss.side[i - 1]);
-    }
-    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i) {
-        e = hipEventRecord(ss.join[i], ss.side[i]);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, ss.join[i], 0);
-    }
-    return e;
+    if (e != hipSuccess) return e;
+    return run_beside(ss, st, a.N, [&](int c, hipStream_t s) {
+        return launch_sweep<NMAX>(std::make_integer_sequence<int, NMAX>{}, a.off + c, grid, a, g, s);
+    });
 }
 
 }  // namespace adj

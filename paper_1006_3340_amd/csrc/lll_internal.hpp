@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "lll.h"
+#include "side_streams.hpp"
 
 namespace lll {
 
@@ -64,11 +65,6 @@ struct MlpBuffers {
     void *zero_params = nullptr;  // zero FP32 + BF16 parameter vectors (first-order runs)
     double *stats = nullptr;
     int64_t stat_waves = 0;
-};
-constexpr int kSideStreams = 3;  // with the caller's stream, the device's four queues
-struct SideStreams {             // launches beside the caller's stream (default priority)
-    hipStream_t side[kSideStreams] = {};
-    hipEvent_t fork = nullptr, join[kSideStreams] = {};
 };
 struct GreeksBuffers {
     SideStreams ss;
