@@ -277,8 +277,9 @@ int lll_price_caplets_static(const lll_term_structure *ts, int64_t n_paths, int 
  * walks back from its fixing over them, on the caller's and three side streams
  * joined to it.  B(0, T_1) is held fixed, so dP/dL0 includes the dependence of
  * B(0, T_*) on the forwards (paper Section 3.3, eq. (caplet)).  The states (about
- * (s N (N+1) / 2 + K + 2 N) x 4 bytes per path) go in chunks of paths within 16 GiB,
- * smaller ones where memory is short; they are
+ * (s N (N+1) / 2 + K + 2 N) x 4 bytes per path) go in chunks of paths: within 16 GiB
+ * or 32,768 paths where that is more, a quarter of the free memory at most, and
+ * smaller ones, down to 64 paths, where an allocation does not fit.  They are
  * allocated on the first call and kept by the plan.  LLL_EUNSUPPORTED for
  * N > LLL_N_MAX.  Asynchronous. */
 int lll_plan_greeks(lll_plan *plan, int64_t n_paths, uint64_t seed, void *stream);

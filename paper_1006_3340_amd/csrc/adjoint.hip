@@ -4,6 +4,7 @@
 #include "adjoint_kernel.hpp"
 #include "lll_device.hpp"
 #include "lll_internal.hpp"
+#include "state_chunk.hpp"
 
 namespace lll {
 namespace adj {
@@ -152,12 +153,6 @@ __global__ void __launch_bounds__(256) reduce_cols_kernel(const double *__restri
 
 namespace {
 
-// The states of the forward pass, the increments, the fixings and the carried
-// adjoint take 4 (s N (N+1) / 2 + K + 2 N) bytes per path (34 KB at 40 rates and 10
-// steps per period): paths go in chunks that keep them within this many bytes
-// (524,000 paths there, 8 wavefronts per SIMD).
-constexpr int64_t kStateBytes = int64_t(16) << 30;
-
 int64_t state_rows(const lll_plan &p) {  // see AdjArgs
     return int64_t(p.s) * (p.N * (p.N + 1) / 2) + p.K + 2 * p.N;
 }
@@ -188,22 +183,24 @@ hipError_t greeks_alloc(lll_plan &p) {
         e = hipStreamCreateWithFlags(&g.ss.side[i], hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&g.ss.join[i], hipEventDisableTiming);
     }
-    if (e != hipSuccess) return e;
-    const int64_t all = (p.max_paths + kBlock - 1) / kBlock * kBlock;
-    int64_t chunk = kStateBytes / (4 * state_rows(p)) / kBlock * kBlock;
-    if (chunk < kBlock) chunk = kBlock;
-    if (chunk > all) chunk = all;
-    for (;; chunk = (chunk / 2 + kBlock - 1) / kBlock * kBlock) {  // less where memory is short
-        e = hipMalloc((void **)&g.rows, (size_t)chunk * 4 * state_rows(p));
-        if (e != hipErrorOutOfMemory || chunk <= 64 * kBlock) break;
-        (void)hipGetLastError();
-    }
     if (e != hipSuccess) {
-        g.rows = nullptr;
+        (void)hipGetLastError();
         return e;
     }
-    g.chunk = chunk;
-    return hipSuccess;
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) free_bytes = size_t(1) << 40;
+    const int64_t per_path = 4 * state_rows(p);
+    g.chunk = alloc_state_chunk(per_path, p.max_paths, static_cast<int64_t>(free_bytes),
+                                [&](int64_t paths) {
+                                    const hipError_t a = hipMalloc((void **)&g.rows, paths * per_path);
+                                    if (a != hipSuccess) {
+                                        g.rows = nullptr;
+                                        (void)hipGetLastError();
+                                    }
+                                    return a;
+                                },
+                                e);
+    return e;
 }
 
 void greeks_free(lll_plan &p) {
@@ -243,7 +240,7 @@ hipError_t adjoint_setup(const lll_plan &p, hipStream_t st, adj::AdjArgs &g) {
 }
 
 // The kernels' arguments for the paths [first, first + chunk) of the pass: its
-// waves' partials, and the states of one chunk.  Chunks are whole blocks, so the
+// waves' partials, and the states of one chunk.  Chunks are whole wavefronts, so the
 // wave sums do not depend on the chunking.
 bool next_chunk(const lll_plan &p, int64_t n_paths, uint64_t seed, int64_t first, int cols,
                 detail::PathArgs<float> &a, adj::AdjArgs &g) {
