@@ -858,7 +858,8 @@ static int greeks_prepare(lll_plan *plan, int64_t n_paths) {
 int lll_plan_greeks(lll_plan *plan, int64_t n_paths, uint64_t seed, void *stream) {
     const int rc = greeks_prepare(plan, n_paths);
     if (rc != LLL_OK) return rc;
-    hipError_t e = hipSuccess;
+    hipError_t e = lll::greeks_streams(*plan);
+    if (e != hipSuccess) return hip_fail(e, "creating the sweeps' streams");
     hipStream_t st = as_stream(stream);
     const bool t = plan->timing;
     // the whole Greeks pass is timed as the path stage (events 1 -> 2)

@@ -178,11 +178,6 @@ hipError_t greeks_alloc(lll_plan &p) {
     A((void **)&g.vjp_out, 3 * N * sizeof(double));
     A((void **)&g.vjp_g, N * sizeof(double));
     A((void **)&g.vjp_w, N * sizeof(float));
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&g.ss.fork, hipEventDisableTiming);
-    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i) {
-        e = hipStreamCreateWithFlags(&g.ss.side[i], hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&g.ss.join[i], hipEventDisableTiming);
-    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return e;
@@ -200,6 +195,18 @@ hipError_t greeks_alloc(lll_plan &p) {
                                     return a;
                                 },
                                 e);
+    return e;
+}
+
+// The streams of the Jacobian's sweeps (a vector-Jacobian product uses none).
+hipError_t greeks_streams(lll_plan &p) {
+    SideStreams &ss = p.g.ss;
+    hipError_t e = ss.fork ? hipSuccess : hipEventCreateWithFlags(&ss.fork, hipEventDisableTiming);
+    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i) {
+        if (!ss.side[i]) e = hipStreamCreateWithFlags(&ss.side[i], hipStreamNonBlocking);
+        if (e == hipSuccess && !ss.join[i])
+            e = hipEventCreateWithFlags(&ss.join[i], hipEventDisableTiming);
+    }
     return e;
 }
 

@@ -139,6 +139,7 @@ hipError_t launch_first_order_tables(const lll_plan &p, hipStream_t st);
 
 // adjoint.hip
 hipError_t greeks_alloc(lll_plan &p);
+hipError_t greeks_streams(lll_plan &p);
 void greeks_free(lll_plan &p);
 hipError_t launch_greeks(const lll_plan &p, int64_t n_paths, uint64_t seed, hipStream_t st);
 hipError_t launch_greeks_vjp(const lll_plan &p, int64_t n_paths, uint64_t seed,
