@@ -176,29 +176,35 @@ def cpu_baseline(ts, n_sample: int, schemes) -> dict:
                            "sample": f"{n1} paths, {dt1:.1f} s"}}
 
 
+def reverse_step_flops(n: int, q: int) -> int:
+    """FP32 flops of one reverse step with n carried rates and q nodes (FMA = 2): per
+    node the suffix products less one (two FMAs for each rate but the lowest) and the
+    upward pass (16 per rate: W Xbar 1, P F 2, the adjoint of ell 2, that of E times x 4,
+    the vol's share 3, F 4); per rate ell 4, the vol adjoint's sum 4, the state's move and
+    its two sums 6."""
+    return q * (4 * (n - 1) + 16 * n) + 14 * n
+
+
 def adjoint_flops_per_path(ts, nodes) -> int:
-    """Algorithmic FP32 flops of the Greeks pass per path: the FULL forward pass,
-    then for every caplet c (n = N - c rates carried) and every step up to its
-    fixing, one recomputed FULL step plus the reverse step (18 flops per
-    (rate, node): suffix product 3, F recursion 5, the adjoints of ell and E 10)."""
+    """FP32 flops the Greeks pass executes per path: the FULL forward pass, then for
+    every caplet c (n = N - c rates carried) a reverse step for every step up to its
+    fixing (the states are kept, not recomputed)."""
     N, s = ts.n_rates, ts.steps_per_period
     total = flops_per_path(ts, "full", nodes)
     for c in range(N):
-        n = N - c
         for q in nodes[:c + 1]:
-            total += s * (flops_per_path_step("full", n, int(q)) + 18 * int(q) * n + 10 * n)
+            total += s * reverse_step_flops(N - c, int(q))
     return total
 
 
 def vjp_flops_per_path(ts, nodes) -> int:
-    """Algorithmic FP32 flops of the vector-Jacobian product per path: the FULL
-    forward pass, then for every period m (n = N - m rates carried) and each of
-    its steps one recomputed FULL step plus the reverse step."""
+    """FP32 flops the vector-Jacobian product executes per path: the FULL forward
+    pass, then for every period m (n = N - m rates carried) a reverse step for each of
+    its steps."""
     N, s = ts.n_rates, ts.steps_per_period
     total = flops_per_path(ts, "full", nodes)
     for m in range(N):
-        n, q = N - m, int(nodes[m])
-        total += s * (flops_per_path_step("full", n, q) + 18 * q * n + 10 * n)
+        total += s * reverse_step_flops(N - m, int(nodes[m]))
     return total
 
 
