@@ -552,8 +552,9 @@ int lll_plan_tables(lll_plan *plan, double *x_host, double *w_host, double *kapp
 /* The nodes on which the kernels integrate the coupling.  The 64-node rule of
  * lll_plan_tables is a discrete measure; each accrual period m uses the Gauss
  * rule of it with the fewest nodes that reproduces its coupling integrals to
- * 2^-30 (FP32 plans) or 2^-47 (FP64 plans) of their value at every state, and
- * the 64 nodes themselves where no such rule of at most 24 nodes exists:
+ * 2^-30 (FP32 plans) or 2^-47 (FP64 plans) at every state -- of their value where the
+ * live vols have one sign, of sum_q W_q |E_i| (prod_{l>i} (1 + ell_l |E_l|) - 1) where they
+ * have both -- and the 64 nodes themselves where no such rule of at most 24 nodes exists:
  * count_host[N] nodes per period, x_host[N][Q] and w_host[N][Q] (entries past
  * the count undefined).  Runs the plan's precompute; any pointer may be NULL. */
 int lll_plan_nodes(lll_plan *plan, int32_t *count_host, double *x_host, double *w_host,

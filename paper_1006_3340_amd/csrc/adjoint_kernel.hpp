@@ -14,12 +14,12 @@
 // those.  Memory: the forward pass keeps the live rates at the start of every step
 // (packed, s N (N+1) / 2 floats per path), the increments and the fixing of every
 // rate, and the sweeps read them back, a step ahead of their use; paths go in
-// chunks (state_chunk.hpp).  Recomputing each period from
-// a checkpoint at its tenor date instead (an increment, a FULL step and the same
-// traffic through a scratch, per step) and three table entries per rate and node
-// took price and gradient of 40 rates from 12.1 to 15.5 ms at 2^18 paths, the
-// Jacobian from 33 to 66 ms at 2^17.  What bounds it now is the vector ALU at the
-// two wavefronts per SIMD that 6 registers per rate leave the wide sweeps.
+// chunks (state_chunk.hpp).  Recomputing each period from a checkpoint at its tenor date
+// instead (an increment, a FULL step and the same traffic through a scratch, per step)
+// and three table entries per rate and node took price and gradient of 40 rates from
+// 12.4 to 15.5 ms at 2^18 paths, the Jacobian from 33 to 66 ms at 2^17.  What bounds it
+// now is the vector ALU at the two wavefronts per SIMD that 9 registers per rate leave the
+// wide sweeps: 0.41 of the FP32 peak.
 //
 // Reverse of one step, per node q (the suffix products less one, R_l = P_l - 1, by a
 // downward pass, then an upward pass with F_l = sum_{i<l} Cbar_i W E_{i,q}

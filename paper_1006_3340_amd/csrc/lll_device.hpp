@@ -53,7 +53,7 @@ __device__ __forceinline__ double uniform24(uint32_t w) {
 
 // A polynomial coefficient as a scalar-register operand: left to itself the
 // compiler copies each FP64 constant into a vector register pair in front of its
-// FMA (55 of the increment's 280 vector instructions).
+// FMA (55 vector instructions of the increment).
 __device__ __forceinline__ double scalar_const(double c) {
 #if defined(__HIP_DEVICE_COMPILE__)
     __asm__ volatile("" : "+s"(c));
@@ -169,8 +169,9 @@ struct StepConsts {
 // root m g^2, and the acceptance u2 <= m / (m + x) reads u2 (g^2 + 1) <= g^2.  So
 // one square root and one reciprocal give V = m rho^2 and sqrt(V) = sqrt(m) rho with
 // rho = 1/g or g, and dH = mu_H dt + beta V + sqrt(V) z2.  Brownian: sqrt(c dt) z1.
-// 110 vector instructions instead of 280; the schemes that do little else
-// (FROZEN, N = 20, 2^20 paths, 400 steps) took 3.3 ms with those.
+// 120 vector instructions instead of 220 (with Philox 165 instead of 270 a step): the
+// scheme that does little else, FROZEN, takes 2.5 ms instead of 3.3 (N = 20, 2^20 paths,
+// 400 steps).
 __device__ __forceinline__ double increment(uint4 w, const StepConsts& sc, bool brownian,
                                             double* V_out) {
     const double r = sqrt_pos(-2.0 * log_unit(uniform24(w.x)));

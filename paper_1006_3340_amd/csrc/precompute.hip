@@ -81,11 +81,13 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 // (error down 50 to 500 times per added node at the light-tailed structures; a
 // factor of 0.45 instead of 0.5 balances its ends, halving the largest error).
 // f keeps one sign in x, so an error relative to the 64-node sum of f that holds
-// at every a bounds the error of every coupling relative to itself, whatever the
-// state.  It is largest at the ends of the range of a: each candidate is checked
-// against the 64-node sums at a = Lambda_+, at -Lambda_- and in the limit a -> 0
-// (f / a -> (e^{lambda x} - 1) x), for the smallest and largest live vol, before it
-// is taken:
+// at every a bounds the error of every coupling, whatever the state: relative to the
+// coupling itself with vols of one sign; with both signs the terms of the average
+// cancel, and it is relative to sum_q W |E_i| (prod_{l>i} (1 + ell_l |E_l|) - 1), at whose
+// rounding the 64 nodes' own sum stands.  The error is largest at the ends of the range of a:
+// each candidate is checked against the 64-node sums at a = Lambda_+, at -Lambda_- and in
+// the limit a -> 0 (f / a -> (e^{lambda x} - 1) x), for the smallest and largest live vol
+// (the vols between them are not checked one by one), before it is taken:
 //   FP32 plans: 2^-30, a 64th of a unit in the last place of the tables;
 //   FP64 plans: 2^-47, the rounding of the 64-term sums.
 // At 64 nodes FULL spent 15.3 of its 19.1 ms (20 rates, 2^20 paths) in the
