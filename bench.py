@@ -33,7 +33,7 @@ PEAK_FP32 = 157.3e12   # MI355X vector FP32, FLOP/s
 # for a 1 GiB device copy (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0;
 # profiles/path_kernel_gpu_n20_counters.md), keyed by the hash of the kernel
 # sources they were taken on; any other hash reports null.
-TRAFFIC_BYTES = {"e1718de725c6d9c2": {"full": 33439120, "picard": 33961152}}
+TRAFFIC_BYTES = {"e1718de725c6d9c2": {"full": 34047664, "picard": 33944896}}
 KERNEL_SOURCES = ["paper_1006_3340_amd/csrc/path_kernel.hpp",
                   "paper_1006_3340_amd/csrc/lll_device.hpp"]
 MLP_SOURCES = ["paper_1006_3340_amd/csrc/mlp_path.hip", "paper_1006_3340_amd/csrc/mlp.hpp",
@@ -43,10 +43,10 @@ MLP_SOURCES = ["paper_1006_3340_amd/csrc/mlp_path.hip", "paper_1006_3340_amd/csr
 # rocprofv3 --pmc figures of the surrogate pricing kernel at 2^20 paths
 # (profiles/mlp_kernels_mlp_n40_mfma_counters.md), by source hash: a changed
 # kernel reports none
-MLP_COUNTERS = {"131c4d14cb85044c": {
+MLP_COUNTERS = {"f366f09814261d0b": {
     "source": "profiles/mlp_kernels_mlp_n40_mfma_counters.md",
-    "mlp_path_kernel_ms": 529.24, "clock_ghz": 2.38,
-    "counted_mfma_flop": 2.178e+14, "counted_mfma_tflops": 411.4,
+    "mlp_path_kernel_ms": 529.22, "clock_ghz": 2.38,
+    "counted_mfma_flop": 2.178e+14, "counted_mfma_tflops": 411.5,
     "mfma_busy": 0.165, "valu_busy": 0.847, "trans_share_of_valu": 0.221}}
 
 

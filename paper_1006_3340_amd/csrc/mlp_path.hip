@@ -122,32 +122,37 @@ __device__ __forceinline__ void dispatch_first_order(std::integer_sequence<int, 
 }
 
 // Quadrature coupling for the judge and the fallback (ell recomputed from the
-// state, which this step has not changed yet), then the state update.
+// state, which this step has not changed yet).  Dispatched apart from the update that every
+// step runs: inside it, its scalar registers cost the first-order pass loads in flight (1,000
+// paths 3.94 ms, 3.84 apart; 2^18 6.91 and 6.73; the network's passes are the same).
+template <int J0>
+__device__ __forceinline__ void quad_step(const PathArgs<float> &a, int k, bool judge, uint64_t oob,
+                                          float (&C)[kSlots], const float (&X)[kSlots],
+                                          float (&st)[kNStat]) {
+    float ell[kSlots], Cq[kSlots];
+#pragma unroll
+    for (int j = J0; j < kSlots; ++j) ell[j] = detail::ell_of(X[j], a.cinv[j]);
+    detail::quad_coupling<float, kSlots, J0>(a.ew + (size_t)k * kQ * kSlots * 2, a.nq[k], ell, Cq);
+#pragma unroll
+    for (int j = J0; j < kSlots; ++j) {
+        if (judge) {
+            const float e = fabsf(C[j] - Cq[j]);
+            st[2] += 1.0f;
+            st[3] += e;
+            st[4] += fabsf(Cq[j]);
+            if (Cq[j] != 0.0f) st[5] = fmaxf(st[5], e / fabsf(Cq[j]));
+        }
+        const bool fb = (oob >> (j + 1)) != 0;
+        st[1] += fb ? 1.0f : 0.0f;
+        C[j] = fb ? Cq[j] : C[j];
+    }
+}
+
+// The state update.
 template <int J0>
 __device__ __forceinline__ void finish_step(const PathArgs<float> &a, int k, float dH,
-                                            bool need_quad, bool judge, uint64_t oob,
-                                            float (&C)[kSlots], float (&X)[kSlots],
+                                            const float (&C)[kSlots], float (&X)[kSlots],
                                             float (&st)[kNStat]) {
-    if (need_quad) {
-        float ell[kSlots], Cq[kSlots];
-#pragma unroll
-        for (int j = J0; j < kSlots; ++j) ell[j] = detail::ell_of(X[j], a.cinv[j]);
-        detail::quad_coupling<float, kSlots, J0>(a.ew + (size_t)k * kQ * kSlots * 2, a.nq[k], ell,
-                                                    Cq);
-#pragma unroll
-        for (int j = J0; j < kSlots; ++j) {
-            if (judge) {
-                const float e = fabsf(C[j] - Cq[j]);
-                st[2] += 1.0f;
-                st[3] += e;
-                st[4] += fabsf(Cq[j]);
-                if (Cq[j] != 0.0f) st[5] = fmaxf(st[5], e / fabsf(Cq[j]));
-            }
-            const bool fb = (oob >> (j + 1)) != 0;
-            st[1] += fb ? 1.0f : 0.0f;
-            C[j] = fb ? Cq[j] : C[j];
-        }
-    }
     const cptr<float> lamk = a.lam + (size_t)k * kSlots;
     const cptr<float> d0k = a.drift0 + (size_t)k * kSlots;
     const float dt = a.dt[k];
@@ -157,12 +162,19 @@ __device__ __forceinline__ void finish_step(const PathArgs<float> &a, int k, flo
 }
 
 template <int... Js>
+__device__ __forceinline__ void dispatch_quad(std::integer_sequence<int, Js...>, int j0,
+                                              const PathArgs<float> &a, int k, bool judge,
+                                              uint64_t oob, float (&C)[kSlots],
+                                              const float (&X)[kSlots], float (&st)[kNStat]) {
+    (void)((j0 == Js ? (quad_step<Js>(a, k, judge, oob, C, X, st), 0) : 0) + ...);
+}
+
+template <int... Js>
 __device__ __forceinline__ void dispatch_finish(std::integer_sequence<int, Js...>, int j0,
                                                 const PathArgs<float> &a, int k, float dH,
-                                                bool need_quad, bool judge, uint64_t oob,
-                                                float (&C)[kSlots], float (&X)[kSlots],
+                                                const float (&C)[kSlots], float (&X)[kSlots],
                                                 float (&st)[kNStat]) {
-    (void)((j0 == Js ? (finish_step<Js>(a, k, dH, need_quad, judge, oob, C, X, st), 0) : 0) + ...);
+    (void)((j0 == Js ? (finish_step<Js>(a, k, dH, C, X, st), 0) : 0) + ...);
 }
 
 // acc[mt] = the biases of this lane's units 16 mt + 4 grp + e (reloaded at
@@ -385,8 +397,9 @@ mlp_path_kernel(PathArgs<float> a, MlpArgs g) {
             }
         }
         const bool need_quad = judge || __any((oob >> (j0 + 1)) != 0);
-        dispatch_finish(std::make_integer_sequence<int, kSlots>{}, j0, a, k, dH, need_quad, judge,
-                        oob, C, X, st);
+        if (need_quad)
+            dispatch_quad(std::make_integer_sequence<int, kSlots>{}, j0, a, k, judge, oob, C, X, st);
+        dispatch_finish(std::make_integer_sequence<int, kSlots>{}, j0, a, k, dH, C, X, st);
         if (++js == a.s) {
             if (SPLIT == 1 || (part == 0 && gid - lane < a.n_paths))
                 detail::dispatch_payoff<float, kSlots, detail::kAnyProduct>(std::make_integer_sequence<int, kSlots>{}, j0, a,
